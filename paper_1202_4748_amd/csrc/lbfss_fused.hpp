@@ -116,6 +116,12 @@ __device__ __forceinline__ void pull_plane(const T *const (&qz)[Q], const PlaneO
 constexpr unsigned vmcnt_wait(int n) { return (unsigned)((n & 15) | ((n >> 4) << 14) | (0x7 << 4) | (0xF << 8)); }
 static_assert(vmcnt_wait(19) == 0x4F73 && vmcnt_wait(0) == 0x0F70, "s_waitcnt encoding");
 
+// Workgroup barrier of the staged kernels: LDS operations done, vector-memory
+// operations left in flight.  __syncthreads() drains every global->LDS copy
+// (the copies write LDS, so its release fence waits vmcnt(0)): the staged
+// plane then had the chemical-potential phase alone to arrive in.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 __device__ __forceinline__ int xcd_tile(int b, int nt) {
     const int per = nt / 8;
     if (b >= per * 8) return b;
@@ -309,8 +315,28 @@ k_fused(const RepDesc *__restrict__ desc, const FusedTile *__restrict__ tiles, c
 // phases of plane p; no registers hold loads in flight.  The arithmetic is
 // the same function calls in the same order as k_fused.
 // ---------------------------------------------------------------------------
-typedef __attribute__((address_space(1))) const void *gptr_t;
 typedef __attribute__((address_space(3))) void *lptr_t;
+
+// Asynchronous copy of 16 (or 4) bytes per lane from g to LDS, lane l of the
+// wave to dst + 16 l (4 l); dst is wave-uniform.  Written as an instruction:
+// the compiler would follow a builtin copy and put a full vmcnt(0) ahead of
+// the first LDS read that may see it, draining the population stores as
+// well; the kernels count the operations themselves (vmcnt_wait).  The copy
+// has no output register, reads its address as it issues, and needs one wait
+// state after the write of M0.  With the copies in flight through the
+// collision and the stores through the next wait: 512^3 FP32 5170 -> 4920 us
+// a step, 512^3 FP16 4.04 -> 3.85 ms, the paper's model at 256^3 577 -> 551.
+template <int BYTES>
+__device__ __forceinline__ void copy_to_lds(const void *g, lptr_t dst) {
+    static_assert(BYTES == 16 || BYTES == 4, "copy widths in use");
+    const uint32_t base = (uint32_t)(uintptr_t)dst;
+    if constexpr (BYTES == 16)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(base), "v"(g)
+                     : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(base), "v"(g)
+                     : "memory");
+}
 
 __device__ __forceinline__ uint32_t pull_off(int q, const PlaneOffs &o) {
     switch (q) {
@@ -341,7 +367,14 @@ __device__ __forceinline__ uint32_t pull_off(int q, const PlaneOffs &o) {
 // 512-thread tiles fit two workgroups per CU (LDS and at most 128 VGPRs)
 // in every instance the host launches; the build checks the VGPR count (a
 // launch-bounds hint to the same effect made the compiler's code slower)
-template <typename T, int TX, int TY, bool ROWS, bool SNAP>
+//
+// DRAIN: wait for the staged copies and the stores at every barrier, as
+// __syncthreads() would.  Where all tiles of the lattice are resident at once
+// this keeps neighbouring tiles in step, so that the halo rows one stages are
+// still in L2 when the next does: 256^3 FP32 on 64 x 8 x 64 (512 tiles on 256
+// CUs) 609 us a step drained, 628 us not; with more tiles than one round the
+// copies are better left in flight (512^3: 5240 us drained, 4920 us not).
+template <typename T, int TX, int TY, bool ROWS, bool SNAP, bool DRAIN = false>
 __global__ void __launch_bounds__(TX * TY)
 k_fused_staged(const RepDesc *__restrict__ desc, const FusedTile *__restrict__ tiles, const T *__restrict__ pop,
                T *__restrict__ pop_out, const uint64_t *__restrict__ step, int koff, int *__restrict__ err,
@@ -486,14 +519,11 @@ k_fused_staged(const RepDesc *__restrict__ desc, const FusedTile *__restrict__ t
 #pragma unroll
                 for (int m = 0; m < NM; ++m)
                     if (r_on[m])
-                        __builtin_amdgcn_global_load_lds((gptr_t)(bq + (row_of(r_row[m], cy_of(q)) + r_col[m])),
-                                                         (lptr_t)&s_stage[q][m * 64 * CH], 16, 0, 0);
+                        copy_to_lds<16>(bq + (row_of(r_row[m], cy_of(q)) + r_col[m]),
+                                        (lptr_t)&s_stage[q][m * 64 * CH]);
             } else {
-                __builtin_amdgcn_global_load_lds((gptr_t)(bq + pull_off(q, io)), (lptr_t)&s_stage[q][wave * 64], 4,
-                                                 0, 0);
-                if (wave < NHW)
-                    __builtin_amdgcn_global_load_lds((gptr_t)(bq + pull_off(q, ho)),
-                                                     (lptr_t)&s_stage[q][NT + wave * 64], 4, 0, 0);
+                copy_to_lds<4>(bq + pull_off(q, io), (lptr_t)&s_stage[q][wave * 64]);
+                if (wave < NHW) copy_to_lds<4>(bq + pull_off(q, ho), (lptr_t)&s_stage[q][NT + wave * 64]);
             }
         }
     };
@@ -517,9 +547,9 @@ k_fused_staged(const RepDesc *__restrict__ desc, const FusedTile *__restrict__ t
     auto body = [&](int p, float(&ld)[Q], float(&cl)[Q]) __attribute__((always_inline)) {
         // 1. staged pulls of plane p have landed (stores of the last collision,
         //    if any, are the only younger memory operations)
-        if (stored_last) __builtin_amdgcn_s_waitcnt(vmcnt_wait(Q));  // the Q stores may still run
+        if (stored_last && !DRAIN) __builtin_amdgcn_s_waitcnt(vmcnt_wait(Q));  // the Q stores may still run
         else __builtin_amdgcn_s_waitcnt(vmcnt_wait(0));
-        __syncthreads();
+        lds_barrier();
         {
             float *rs = s_rho[rslot(p)];
             if (inner) {
@@ -554,7 +584,7 @@ k_fused_staged(const RepDesc *__restrict__ desc, const FusedTile *__restrict__ t
                 rs[r_h2] = drho_of(h);
             }
         }
-        __syncthreads();
+        lds_barrier();
         // 2. prefetch plane p + 1
         if (p + 1 <= tl.z0 + tl.nz + 1) issue(p + 1);
         // 3. chemical potential of plane p - 1
@@ -571,7 +601,8 @@ k_fused_staged(const RepDesc *__restrict__ desc, const FusedTile *__restrict__ t
             if (inner) ms[m_in] = mu_at(r_in);
             if (has_mh) ms[m_h] = mu_at(r_mh);
         }
-        __syncthreads();
+        if (DRAIN) __builtin_amdgcn_s_waitcnt(vmcnt_wait(0));
+        lds_barrier();
         // 4. collision of plane z = p - 2
         stored_last = false;
         if (p - 2 >= tl.z0) {
@@ -735,6 +766,9 @@ inline bool rows_snap_tile(const std::vector<RepDesc> &reps, bool fp32, int tx, 
 }
 
 
+// 64 x 8 tiles resident at once: two workgroups on each of 256 CUs
+constexpr int kOneRound = 512;
+
 template <typename T, bool ROWS, bool SNAP>
 void launch_staged_snap(const RepDesc *desc, const FusedTile *tiles, int n_tiles, const T *in, T *out,
                         const uint64_t *step, int koff, int *err, int tx, int ty, hipStream_t stream, float *snap,
@@ -748,9 +782,15 @@ void launch_staged_snap(const RepDesc *desc, const FusedTile *tiles, int n_tiles
     else if (ROWS && tx == 64 && ty == 4)
         hipLaunchKernelGGL((k_fused_staged<T, 64, 4, true, SNAP>), dim3(n_tiles), dim3(256), 0, stream, desc, tiles,
                            in, out, step, koff, err, snap, total);
-    else if (ROWS && tx == 64 && ty == 8)
-        hipLaunchKernelGGL((k_fused_staged<T, 64, 8, true, SNAP>), dim3(n_tiles), dim3(512), 0, stream, desc, tiles,
-                           in, out, step, koff, err, snap, total);
+    else if (ROWS && tx == 64 && ty == 8) {
+        constexpr bool can_drain = sizeof(T) == 4 && !SNAP;
+        if (can_drain && n_tiles <= kOneRound)
+            hipLaunchKernelGGL((k_fused_staged<T, 64, 8, true, SNAP, can_drain>), dim3(n_tiles), dim3(512), 0, stream,
+                               desc, tiles, in, out, step, koff, err, snap, total);
+        else
+            hipLaunchKernelGGL((k_fused_staged<T, 64, 8, true, SNAP>), dim3(n_tiles), dim3(512), 0, stream, desc,
+                               tiles, in, out, step, koff, err, snap, total);
+    }
     else
         hipLaunchKernelGGL((k_fused_staged<T, 32, 8, ROWS, SNAP>), dim3(n_tiles), dim3(256), 0, stream, desc, tiles,
                            in, out, step, koff, err, snap, total);

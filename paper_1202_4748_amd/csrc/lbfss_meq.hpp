@@ -366,8 +366,7 @@ k_meq_staged(const RepDesc *__restrict__ desc, const FusedTile *__restrict__ til
 #pragma unroll
             for (int m = 0; m < NM; ++m)
                 if (r_on[m])
-                    __builtin_amdgcn_global_load_lds((gptr_t)(bq + r_row[m][cy_of(q) + 1] + r_col[m]),
-                                                     (lptr_t)&s_stage[q][m * 64 * CH], 16, 0, 0);
+                    copy_to_lds<16>(bq + r_row[m][cy_of(q) + 1] + r_col[m], (lptr_t)&s_stage[q][m * 64 * CH]);
         }
     };
 
@@ -379,7 +378,7 @@ k_meq_staged(const RepDesc *__restrict__ desc, const FusedTile *__restrict__ til
         //    collision, if any, are the only younger memory operations)
         if (stored_last) __builtin_amdgcn_s_waitcnt(vmcnt_wait(Q));  // the Q stores may still run
         else __builtin_amdgcn_s_waitcnt(vmcnt_wait(0));
-        __syncthreads();
+        lds_barrier();
         {
             float *rs = s_rho[rslot(p)];
             if (inner) {
@@ -394,7 +393,7 @@ k_meq_staged(const RepDesc *__restrict__ desc, const FusedTile *__restrict__ til
                 rs[r_h] = drho_of(h);
             }
         }
-        __syncthreads();
+        lds_barrier();
         // 2. prefetch plane p + 1
         if (p + 1 <= tl.z0 + tl.nz) issue(p + 1);
         // 3. collision of plane z = p - 1 (densities of z - 1, z, z + 1 in the ring)
