@@ -88,7 +88,8 @@ enum {
                          * raises LB_EUNSTABLE.  Mass and momentum are conserved exactly.
                          * Plans: LB_KERNEL_SPLIT (a density pass and a collide pass) or
                          * LB_KERNEL_ROWS (one z-marching pass with a one-site density
-                         * halo; tiles (64,4), (32,8), (16,16), (64,8), (32,16)); the two
+                         * halo; tiles (64,4), (32,8), (16,16), (64,8), (32,16); (32,8)
+                         * tiles of one or two planes as blocks, see lb_plan); the two
                          * give identical results.  FP32 storage only (at rest this model
                          * keeps nearly all mass on the rest population, so the stored
                          * deviations are O(1)); not with LB_FORCE_OFF; equal in a batch. */
@@ -160,8 +161,7 @@ typedef struct {
 
 /* launch plans (results do not depend on the plan) */
 enum {
-    LB_KERNEL_SPLIT = 0,  /* density pass, chemical-potential pass, collide pass (with
-                           * LB_EQ_PRESSURE: density pass, collide pass) */
+    LB_KERNEL_SPLIT = 0,  /* density pass, collide pass (which forms the chemical potential) */
     LB_KERNEL_FUSED = 1,  /* one z-marching pass, density halo in LDS, pulls in registers */
     LB_KERNEL_STAGED = 2, /* as FUSED, the next plane's pulls staged asynchronously in LDS
                            * (FP32 storage; FP16 handles run FUSED) */
@@ -178,7 +178,9 @@ typedef struct {
                           * with LB_EQ_PRESSURE rows only, in {(64,4), (32,8), (16,16),
                           * (64,8), (32,16)}; clamped to L */
     int32_t tile_y;      /* fused: tile edge along y */
-    int32_t tile_z;      /* fused: planes marched by one workgroup */
+    int32_t tile_z;      /* fused: planes marched by one workgroup.  Shallow tiles, (16,8)
+                          * of 1 or 4 planes, (32,8) of 4 (LB_EQ_PRESSURE: of 1 or 2),
+                          * are not marched but taken as one block */
     int32_t graph_steps; /* > 0: capture this many steps in a HIP graph and replay
                           * it, rounded up to a multiple of the sampling period
                           * (sample_every, times sk3_stride when set, doubled if odd;
@@ -197,12 +199,13 @@ typedef struct lb_sim lb_sim; /* opaque, owned by the library */
  * init_sigma g with g the first Box-Muller normal of Philox call
  * (site, 0, 1 << 16, 0), u = 0, f_i = w_i rho.  *out receives the handle
  * (owned by the library until lb_destroy); p is read during the call only.
- * Initial plan: LB_KERNEL_ROWS where every L allows it (else FUSED, or SPLIT
- * with LB_EQ_PRESSURE); when the largest L is at least 256 (FP32) on 64 x 8
- * tiles in four z slabs (six from L = 512), from 128 to 255 (FP32) on 64 x 4
- * tiles in three, from 128 (FP16) on 64 x 8 tiles in six, from 128
- * (LB_EQ_PRESSURE) on 64 x 8 tiles in eight, else on 32 x 8 tiles; direct
- * launches (lb_set_plan and lb_tune change it; results do not depend on it).
+ * Initial plan, by size: blocks (lb_plan, tile_z) while they fit one round of
+ * the chip, LB_KERNEL_SPLIT up to 160^3 sites (115^3 in FP16, never with
+ * LB_EQ_PRESSURE) and wherever the edges do not allow LB_KERNEL_ROWS, else
+ * LB_KERNEL_ROWS: on 32 x 8 or 64 x 8 tiles, from L = 256 on 64 x 8 tiles in
+ * four z slabs (six from L = 512 and in FP16, eight with LB_EQ_PRESSURE);
+ * direct launches (lb_set_plan and lb_tune change it; results do not depend
+ * on it).
  * Errors: LB_EINVAL for L < 4, L > 1024, tau <= 1/2, kT < 0, kappa < 0,
  * b < 0, rho_c <= 0, init_sigma < 0, bad storage, flags, sample_every < 0,
  * n_levels < 0 or series_capacity < 0; LB_ENOMEM; LB_EDEVICE. */

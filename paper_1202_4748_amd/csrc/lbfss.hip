@@ -18,6 +18,7 @@
 #include "lbfss_sk3.hpp"
 #include "lbfss_d2q9.hpp"
 #include "lbfss_meq.hpp"
+#include "lbfss_block.hpp"
 
 using namespace lbfss;
 
@@ -78,7 +79,7 @@ struct lb_sim {
     int64_t device_bytes = 0;
 
     int storage = LB_FP32;
-    bool eq_pressure = false;  // LB_EQ_PRESSURE: the paper's model (split kernels)
+    bool eq_pressure = false;  // LB_EQ_PRESSURE: the paper's model
     int nrep = 0;
     std::vector<int> L;
     std::vector<lb_params> P;
@@ -91,7 +92,6 @@ struct lb_sim {
     float *d_sigma0 = nullptr;
     void *pop[2] = {nullptr, nullptr};
     float *d_drho = nullptr;
-    float *d_mu = nullptr;
     uint64_t *d_step = nullptr;
     int *d_err = nullptr;
 
@@ -256,8 +256,15 @@ void launch_step(lb_sim *s, int cur, int koff, float *snap) {
     const T *in = (const T *)s->pop[cur];
     T *out = (T *)s->pop[cur ^ 1];
     const int64_t total = s->total_sites;
+    const BlockArgs blk{s->d_desc, s->d_tiles, s->n_tiles, s->d_step, koff, s->d_err, snap, total, s->stream};
+    const bool tiled = s->plan.kernel != LB_KERNEL_SPLIT && s->n_tiles > 0;
+    const bool block = tiled && block_tile(s->eq_pressure, s->plan.tile_x, s->plan.tile_y, s->plan.tile_z);
     if (s->eq_pressure) {
         if constexpr (std::is_same<T, float>::value) {  // the model keeps FP32 storage
+            if (block) {
+                launch_block_eq(blk, s->plan.tile_z, in, out);
+                return;
+            }
             if (s->plan.kernel == LB_KERNEL_ROWS && s->n_tiles > 0) {
                 launch_meq_staged(s->d_desc, s->d_tiles, s->n_tiles, in, out, s->d_step, koff, s->d_err,
                                   s->plan.tile_x, s->plan.tile_y, s->stream, snap, total);
@@ -275,6 +282,10 @@ void launch_step(lb_sim *s, int cur, int koff, float *snap) {
             hipLaunchKernelGGL((k_meq_collide<T, false>), dim3((unsigned)nb), dim3(kBlock), 0, s->stream, s->d_desc,
                                s->nrep, s->total_sites, in, out, (const float *)s->d_drho,
                                (const uint64_t *)s->d_step, koff, s->d_err, snap);
+        return;
+    }
+    if (block) {
+        launch_block<T>(blk, s->plan.tile_x, s->plan.tile_z, in, out);
         return;
     }
     if (s->plan.kernel == LB_KERNEL_ROWS && s->n_tiles > 0) {
@@ -300,16 +311,7 @@ void launch_step(lb_sim *s, int cur, int koff, float *snap) {
     const int64_t nb = ceil_div(s->total_sites, kBlock);
     hipLaunchKernelGGL(k_density<T>, dim3((unsigned)nb), dim3(kBlock), 0, s->stream, s->d_desc, s->nrep,
                        s->total_sites, in, s->d_drho);
-    hipLaunchKernelGGL(k_chem_potential, dim3((unsigned)nb), dim3(kBlock), 0, s->stream, s->d_desc, s->nrep,
-                       s->total_sites, (const float *)s->d_drho, s->d_mu);
-    if (snap)
-        hipLaunchKernelGGL((k_collide<T, true>), dim3((unsigned)nb), dim3(kBlock), 0, s->stream, s->d_desc,
-                           s->nrep, s->total_sites, in, out, (const float *)s->d_drho, (const float *)s->d_mu,
-                           (const uint64_t *)s->d_step, koff, s->d_err, snap);
-    else
-        hipLaunchKernelGGL((k_collide<T, false>), dim3((unsigned)nb), dim3(kBlock), 0, s->stream, s->d_desc,
-                           s->nrep, s->total_sites, in, out, (const float *)s->d_drho, (const float *)s->d_mu,
-                           (const uint64_t *)s->d_step, koff, s->d_err, snap);
+    launch_block_split<T>(blk, in, out, s->d_drho);
 }
 
 // One step; with snap set the step kernel also writes the sample snapshot of
@@ -776,6 +778,78 @@ int build_snap_tiles(lb_sim *s, const lb_plan &p) {
     return LB_OK;
 }
 
+// Blocks (or tiles) of a shape over all replicas, and the sites they span.
+void count_tiles(const lb_sim *s, int tx, int ty, int tz, int64_t *n, int64_t *span) {
+    *n = *span = 0;
+    for (int L : s->L) {
+        const int64_t c = ceil_div(L, tx) * ceil_div(L, ty) * ceil_div(L, tz);
+        *n += c;
+        *span += c * tx * ty * tz;
+    }
+}
+
+// The plan of a new handle, by size: blocks while they are resident in one
+// round of the 256 CUs, then two passes, then marching tiles (us a step,
+// force model FP32 unless stated).
+lb_plan default_plan(const lb_sim *s) {
+    const bool rows = rows_ok(s), fp16 = s->storage == LB_FP16;
+    const int64_t T = s->total_sites;
+    const int maxL = s->max_L, march = rows ? LB_KERNEL_ROWS : LB_KERNEL_FUSED;
+    int64_t n, span;
+    if (s->eq_pressure) {
+        if (!rows) return lb_plan{LB_KERNEL_SPLIT, 0, 0, 0, 0, 0};
+        // 32^3: 7.4, marching 45; 64^3: 13.3, 46; 112^3: 59 against 70; 128^3: 113 against 80
+        count_tiles(s, 32, 8, 1, &n, &span);
+        if (n <= 256) return lb_plan{march, 32, 8, 1, 0, 0};
+        if (T < 118 * 118 * 118) return lb_plan{march, 32, 8, 2, 0, 0};
+    } else {
+        // 32^3: 7.7 as 256 blocks of 16 x 8 x 1, 8.7 as 128 of twice the
+        // depth, 10.3 in three passes, marching 54
+        count_tiles(s, 16, 8, 1, &n, &span);
+        if (n <= 256) return lb_plan{march, 16, 8, 1, 0, 0};
+        // deeper blocks where the lattice's edge leaves few of their threads
+        // idle: 48^3 12.1 against 15.2 in two passes (40^3, padded by a
+        // fifth: 13.4 against 11.8), 64^3 15.8 against 16.2 (FP16 13.5, 15.9)
+        for (int tx : {16, 32}) {
+            count_tiles(s, tx, 8, 4, &n, &span);
+            if (n <= 256 && 5 * span < 6 * T) return lb_plan{march, tx, 8, 4, 0, 0};
+        }
+        // two passes read the populations twice, but every CU is at work:
+        // 96^3 41 against 51 on the best marching tiles, 144^3 150 against
+        // 156, 160^3 192 against 198, 176^3 279 against 237; FP16 112^3 54
+        // against 58, 128^3 69 against 60.  Without rows staging (an edge
+        // that is no multiple of 4, FP16 of 8) they stay ahead: 250^3 859
+        // against 1183.  A batch of small lattices marches from 2^21 sites
+        // (96-replica sweep: 130 against 139).
+        const int64_t two = fp16 ? 116 * 116 * 116 : (maxL < 128 ? 128 * 128 * 128 : 161 * 161 * 161);
+        if (!rows || T < two) return lb_plan{LB_KERNEL_SPLIT, 0, 0, 0, 0, 0};
+    }
+    lb_plan p{LB_KERNEL_ROWS, 32, 8, 12, 0, 0};  // sweep: 12 planes 130, 16 planes 147, 8 planes 135
+    if (maxL < 116) return p;
+    // 64 x 8 tiles stage the fewest halo rows a site (512 threads, two
+    // workgroups per CU); below 256 FP32 they give way to 32 x 8 where the
+    // last tile of a row would be mostly empty (224^3: 498 against 515)
+    const int64_t wide_span = ceil_div(maxL, 64) * 64;
+    if (!fp16 && maxL < 256 && 8 * wide_span > 9 * maxL) {
+        p.tile_z = 16;
+        return p;
+    }
+    p.tile_x = 64;
+    // shallow slabs until their tiles fill the chip: 128^3 eq 80.7 in eight
+    // planes, 81.8 in sixteen, 136 in 32; 192^3 309 in sixteen, 303 in 32,
+    // 340 in 64 on 64 x 4 tiles; 240^3 618 in sixteen, 586 in 32
+    if (maxL <= 128) p.tile_z = 8;
+    else if (maxL < 224 || (fp16 && maxL < 256)) p.tile_z = 16;
+    else if (s->eq_pressure) p.tile_z = (maxL + 7) / 8;  // 256^3: eight slabs 551; three 5% slower
+    else if (fp16) p.tile_z = (maxL + 5) / 6;
+    else if (maxL < 256) p.tile_z = 32;
+    // four slabs while one layer of tiles cannot fill a round of two
+    // workgroups per CU (256^3: 512 tiles, one round), else six (512^3: 7%
+    // faster than four)
+    else p.tile_z = ceil_div(maxL, 64) * ceil_div(maxL, 8) >= 512 ? (maxL + 5) / 6 : (maxL + 3) / 4;
+    return p;
+}
+
 int create_impl(int n, const int *L, const lb_params *p, const uint64_t *seeds, lb_sim **out) {
     if (!out || n < 1 || !L || !p || !seeds) return LB_EINVAL;
     *out = nullptr;
@@ -843,10 +917,9 @@ int create_impl(int n, const int *L, const lb_params *p, const uint64_t *seeds, 
         if (!s->pop[b]) return fail(LB_ENOMEM);
     }
     s->d_drho = (float *)dev_alloc(s, sizeof(float) * s->total_sites);
-    s->d_mu = (float *)dev_alloc(s, sizeof(float) * s->total_sites);
     s->d_step = (uint64_t *)dev_alloc(s, sizeof(uint64_t));
     s->d_err = (int *)dev_alloc(s, sizeof(int));
-    if (!s->d_drho || !s->d_mu || !s->d_step || !s->d_err) return fail(LB_ENOMEM);
+    if (!s->d_drho || !s->d_step || !s->d_err) return fail(LB_ENOMEM);
     if ((rc = upload(s, &s->d_desc, s->hdesc))) return fail(rc);
     if ((rc = upload(s, &s->d_sigma0, sigma0))) return fail(rc);
     if (hipMemsetAsync(s->d_step, 0, sizeof(uint64_t), s->stream) != hipSuccess) return fail(LB_EDEVICE);
@@ -863,37 +936,7 @@ int create_impl(int n, const int *L, const lb_params *p, const uint64_t *seeds, 
     if (hipGetLastError() != hipSuccess) return fail(LB_EDEVICE);
     if ((rc = build_sampling(s))) return fail(rc);
     if ((rc = build_sk3(s))) return fail(rc);
-    // default plan: the fused kernel, with rows staging where it applies
-    lb_plan def{LB_KERNEL_FUSED, 32, 8, 16, 0, 0};
-    default_fused_tile(s->hdesc, def.tile_x, def.tile_y, def.tile_z);
-    if (rows_ok(s)) {
-        def.kernel = LB_KERNEL_ROWS;
-        // large lattices, wider source rows: FP32 from L = 256 on 64 x 8
-        // tiles (a quarter fewer staged bytes per site than 64 x 4; 9% faster
-        // at 256^3), in four z slabs while one slab layer of tiles cannot fill
-        // a round of two 512-thread workgroups per CU (L = 256: 512 tiles, one
-        // round), else in six (L = 512: 7% faster than four); below L = 256 on
-        // 64 x 4 tiles in three (three workgroups per CU); FP16 on 64 x 8
-        // tiles in six (64 x 4 measured 5%, 32 x 8 15% slower)
-        int maxL = 0;
-        for (const auto &d : s->hdesc) maxL = std::max(maxL, d.L);
-        if (maxL >= 128) {
-            const bool wide = s->storage == LB_FP16 || maxL >= 256;
-            const int64_t layer = ceil_div(maxL, 64) * ceil_div(maxL, 8);
-            def.tile_x = 64;
-            def.tile_y = wide ? 8 : 4;
-            def.tile_z = !wide ? (maxL + 2) / 3
-                               : (s->storage == LB_FP16 || layer >= 512 ? (maxL + 5) / 6 : (maxL + 3) / 4);
-            // the paper's model (k_meq_staged) on 64 x 8 tiles (512 threads,
-            // 62.6 KB of LDS, two workgroups per CU) in eight slabs: as fast
-            // as 64 x 4 tiles with 17% less HBM traffic (reads 1.13x against
-            // 1.57x the algorithmic bytes); three slabs measured 5% slower
-            if (s->eq_pressure) {
-                def.tile_y = 8;
-                def.tile_z = (maxL + 7) / 8;
-            }
-        }
-    }
+    lb_plan def = default_plan(s);
     if (lb_set_plan(s, &def) != LB_OK) {
         lb_plan split{LB_KERNEL_SPLIT, 0, 0, 0, 0, 0};
         if ((rc = lb_set_plan(s, &split))) return fail(rc);
@@ -1348,6 +1391,8 @@ int lb_set_plan(lb_sim *s, const lb_plan *plan) {
         if (rc) return rc;
     } else if (p.kernel != LB_KERNEL_SPLIT) {
         return LB_EINVAL;
+    } else if (!s->eq_pressure) {  // the collide pass has tiles of its own
+        if (int rc = build_tiles(s, kSplitTX, kSplitTY, kSplitTZ)) return rc;
     }
     if (int rc = build_snap_tiles(s, p)) return rc;
     if (p.kernel != s->plan.kernel || p.tile_x != s->plan.tile_x || p.tile_y != s->plan.tile_y ||
@@ -1367,7 +1412,11 @@ int lb_tune(lb_sim *s, int steps, lb_plan *best) {
     if (!s || steps < 1) return LB_EINVAL;
     std::vector<lb_plan> cands;
     cands.push_back(lb_plan{LB_KERNEL_SPLIT, 0, 0, 0, 0, 0});
-    for (const auto &t : fused_tile_candidates(s->hdesc)) {
+    for (const auto &t : fused_tile_candidates(s->hdesc, s->eq_pressure)) {
+        if (block_tile(s->eq_pressure, t[0], t[1], t[2])) {  // the same kernel under each name
+            cands.push_back(lb_plan{rows_ok(s) ? LB_KERNEL_ROWS : LB_KERNEL_FUSED, t[0], t[1], t[2], 0, 0});
+            continue;
+        }
         cands.push_back(lb_plan{LB_KERNEL_FUSED, t[0], t[1], t[2], 0, 0});
         if (s->storage == LB_FP32 && staged_tile_ok(t[0], t[1]))
             cands.push_back(lb_plan{LB_KERNEL_STAGED, t[0], t[1], t[2], 0, 0});

@@ -679,21 +679,21 @@ inline int make_fused_tiles(const std::vector<RepDesc> &reps, int tx, int ty, in
     return 0;
 }
 
-inline void default_fused_tile(const std::vector<RepDesc> &reps, int &tx, int &ty, int &tz) {
+inline std::vector<std::array<int, 3>> fused_tile_candidates(const std::vector<RepDesc> &reps, bool eq) {
     int maxL = 0;
-    for (const auto &d : reps) maxL = std::max(maxL, d.L);
-    tx = 32;
-    ty = 8;
-    // six z slabs per column on large lattices: 2 x 768 tiles at L = 256
-    // fill 256 CUs holding three workgroups each in two even rounds
-    tz = maxL >= 128 ? (maxL + 5) / 6 : std::min(maxL, 16);
-}
-
-inline std::vector<std::array<int, 3>> fused_tile_candidates(const std::vector<RepDesc> &reps) {
-    int maxL = 0;
-    for (const auto &d : reps) maxL = std::max(maxL, d.L);
+    int64_t sites = 0;
+    for (const auto &d : reps) {
+        maxL = std::max(maxL, d.L);
+        sites += d.N;
+    }
     std::vector<std::array<int, 3>> c;
-    std::vector<int> tzs{16, 32, 64};
+    // blocks (see block_tile), behind the marching tiles on large lattices
+    if (sites < (1 << 22)) {
+        if (eq) c = {{32, 8, 1}, {32, 8, 2}};
+        else c = {{16, 8, 1}, {16, 8, 4}, {32, 8, 4}};
+    }
+    std::vector<int> tzs{8, 12, 16, 32, 64};
+    if (maxL >= 256) tzs.erase(tzs.begin(), tzs.begin() + 2);
     for (int n : {3, 6})
         if ((maxL + n - 1) / n > 16 && std::find(tzs.begin(), tzs.end(), (maxL + n - 1) / n) == tzs.end())
             tzs.push_back((maxL + n - 1) / n);

@@ -1,5 +1,5 @@
-// Step kernels of the split plan (density pass, chemical-potential pass,
-// collide pass), the initial state, and field import/export.
+// The density pass of the split plans, the initial state, and field
+// import/export.
 //
 // Every kernel works on the handle's flattened site index g (all replicas
 // back to back); the replica of g is found by binary search over site_off.
@@ -201,22 +201,6 @@ k_density(const RepDesc *__restrict__ desc, int nrep, int64_t total, const T *__
     drho[g] = drho_of(f);
 }
 
-// Split plan, pass 2: mu = a drho + b drho^3 - kappa lap(drho).
-__global__ void __launch_bounds__(kBlock)
-k_chem_potential(const RepDesc *__restrict__ desc, int nrep, int64_t total,
-                 const float *__restrict__ drho, float *__restrict__ mu) {
-    const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (g >= total) return;
-    const int r = find_rep(desc, nrep, g);
-    const RepDesc &d = desc[r];
-    const Nbr n(g - d.site_off, d.L);
-    const float *dr = drho + d.site_off;
-    const float c = dr[n.x + n.Y0 + n.Z0];
-    mu[g] = chem_potential(d, c, lap18(c, NbrAt{dr, n}));
-}
-
-// Split plan, pass 3: force, collision, noise; the post-collision values are
-// written in place of the site (pull streaming reads them next step).
 // Sample snapshot written by a step kernel: density deviation and momentum
 // of the pulled (pre-collision) populations of flattened site g, which are
 // the state the previous step left (the functions k_snapshot uses, so both
@@ -229,43 +213,6 @@ __device__ __forceinline__ void write_snapshot(float *__restrict__ snap, int64_t
     snap[total + g] = jx;
     snap[2 * total + g] = jy;
     snap[3 * total + g] = jz;
-}
-
-template <typename T, bool SNAP>
-__global__ void __launch_bounds__(kBlock)
-k_collide(const RepDesc *__restrict__ desc, int nrep, int64_t total, const T *__restrict__ pop,
-          T *__restrict__ pop_out, const float *__restrict__ drho, const float *__restrict__ mu,
-          const uint64_t *__restrict__ step, int koff, int *__restrict__ err, float *__restrict__ snap) {
-    const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (g >= total) return;
-    const int r = find_rep(desc, nrep, g);
-    const RepDesc &d = desc[r];
-    const int64_t s = g - d.site_off;
-    const Nbr n(s, d.L);
-    const float *dr = drho + d.site_off;
-    const float *mr = mu + d.site_off;
-    float Fx = 0.f, Fy = 0.f, Fz = 0.f;
-    if (!(d.flags & 1)) {
-        // F = -rho grad(mu) + c_s^2 grad(drho) = grad of psi(y) = drho(y)/3 - rho(x) mu(y)
-        const float rho_x = d.rho_c + dr[s];
-        const NbrAt R{dr, n}, M{mr, n};
-        const Grad18 gr = grad18([&](int dx, int dy, int dz) {
-            return (1.0f / 3.0f) * R(dx, dy, dz) - rho_x * M(dx, dy, dz);
-        });
-        Fx = gr.gx;
-        Fy = gr.gy;
-        Fz = gr.gz;
-    }
-    float f[Q];
-    pull(pop + Q * d.site_off, d.N, n, f);
-    if constexpr (SNAP) write_snapshot(snap, total, g, f);
-    const uint64_t t = *step + (uint64_t)koff;
-    const SiteNoise noise{(uint32_t)s, (uint32_t)t, (uint32_t)(t >> 32), d.key0, d.key1};
-    const float rho = collide_site(d, f, Fx, Fy, Fz, noise);
-    if (!(rho > 0.0f && rho < 1e30f)) *err = 1;  // Sec. III B: rho must stay positive
-    T *out = pop_out + Q * d.site_off;
-#pragma unroll
-    for (int q = 0; q < Q; ++q) Store<T>::st(out + q * d.N, s, f[q]);
 }
 
 // ---------------------------------------------------------------------------
