@@ -78,6 +78,7 @@ k_block(const RepDesc *__restrict__ desc, const FusedTile *__restrict__ tiles, c
     __shared__ float s_noise[SPREAD ? 16 * NS : 1];
 
     const FusedTile tl = tiles[xcd_tile(blockIdx.x, gridDim.x)];
+    if (tl.nz == 0) return;              // padding of a batch's table (whole workgroup)
     const RepDesc d = desc[tl.rep];      // a copy: its loads go out here, not behind the barriers
     const int L = d.L;
     const float rL = __builtin_amdgcn_rcpf((float)L);

@@ -139,6 +139,7 @@ k_fused(const RepDesc *__restrict__ desc, const FusedTile *__restrict__ tiles, c
     __shared__ float s_mu[4][MP];
 
     const FusedTile tl = tiles[xcd_tile(blockIdx.x, gridDim.x)];
+    if (tl.nz == 0) return;  // padding of a batch's table (whole workgroup)
     const RepDesc &d = desc[tl.rep];
     const int L = d.L;
     const uint32_t N = (uint32_t)d.N, LL = (uint32_t)(L * L);
@@ -405,6 +406,7 @@ k_fused_staged(const RepDesc *__restrict__ desc, const FusedTile *__restrict__ t
     auto mslot = [](int p) { return (p + 8) & 1; };
 
     const FusedTile tl = tiles[xcd_tile(blockIdx.x, gridDim.x)];
+    if (tl.nz == 0) return;  // padding of a batch's table (whole workgroup)
     const RepDesc &d = desc[tl.rep];
     const int L = d.L;
     const uint32_t N = (uint32_t)d.N, LL = (uint32_t)(L * L);
@@ -663,19 +665,43 @@ inline bool fused_tile_ok(int tx, int ty) {
     return (tx == 16 && ty == 16) || (tx == 32 && ty == 8) || (tx == 16 && ty == 8) || (tx == 64 && ty == 4);
 }
 
+// The tile table of a plan: x fastest, then y, then z, which xcd_tile deals to
+// the XCDs in contiguous runs.  Replicas of a batch are dealt whole, the
+// largest first, each to the XCD with the least work so far, and the shorter
+// lists are filled with empty tiles: with one run over all replicas some XCDs
+// held only tiles of the large lattices and finished last (96-replica sweep on
+// 32 x 8 x 12: 136 us a step in order, 130 us dealt).
 inline int make_fused_tiles(const std::vector<RepDesc> &reps, int tx, int ty, int tz,
                             std::vector<FusedTile> &out) {
     if (tx < 1 || ty < 1 || tz < 1 || tz > 1024) return -1;
+    constexpr int NX = 8;  // XCDs
     out.clear();
-    for (size_t r = 0; r < reps.size(); ++r) {
+    std::vector<size_t> order(reps.size());
+    for (size_t r = 0; r < reps.size(); ++r) order[r] = r;
+    std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return reps[a].L > reps[b].L; });
+    std::array<std::vector<FusedTile>, NX> lists;
+    std::array<int64_t, NX> work{};
+    const int n_lists = reps.size() > 1 ? NX : 1;
+    for (size_t r : order) {
         const int L = reps[r].L;
         const int nx = std::min(tx, L), ny = std::min(ty, L), nz = std::min(tz, L);
+        const int k = (int)(std::min_element(work.begin(), work.begin() + n_lists) - work.begin());
         for (int z0 = 0; z0 < L; z0 += nz)
             for (int y0 = 0; y0 < L; y0 += ny)
-                for (int x0 = 0; x0 < L; x0 += nx)
-                    out.push_back(FusedTile{(int32_t)r, x0, y0, z0, std::min(nx, L - x0), std::min(ny, L - y0),
-                                            std::min(nz, L - z0), 0});
+                for (int x0 = 0; x0 < L; x0 += nx) {
+                    lists[k].push_back(FusedTile{(int32_t)r, x0, y0, z0, std::min(nx, L - x0), std::min(ny, L - y0),
+                                                 std::min(nz, L - z0), 0});
+                    work[k] += lists[k].back().nz + 4;  // planes marched
+                }
     }
+    if (n_lists == 1) {
+        out = std::move(lists[0]);
+        return 0;
+    }
+    size_t per = 0;
+    for (const auto &l : lists) per = std::max(per, l.size());
+    out.assign(per * NX, FusedTile{0, 0, 0, 0, 0, 0, 0, 0});
+    for (int k = 0; k < NX; ++k) std::copy(lists[k].begin(), lists[k].end(), out.begin() + per * k);
     return 0;
 }
 

@@ -297,6 +297,7 @@ k_meq_staged(const RepDesc *__restrict__ desc, const FusedTile *__restrict__ til
     auto rslot = [](int p) { return (p + 6) % 3; };  // p >= -6
 
     const FusedTile tl = tiles[xcd_tile(blockIdx.x, gridDim.x)];
+    if (tl.nz == 0) return;  // padding of a batch's table (whole workgroup)
     const RepDesc &d = desc[tl.rep];
     const int L = d.L;
     const uint32_t N = (uint32_t)d.N, LL = (uint32_t)(L * L);

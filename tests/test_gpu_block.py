@@ -52,6 +52,24 @@ def test_force_off_and_graph():
         _same(_state(lbf, 20, kernel, tile, steps=12, graph=6, force_off=True), ref)
 
 
+@pytest.mark.parametrize("kernel,tile", [("rows", (16, 8, 4)), ("split", (0, 0, 0)), ("rows", (32, 8, 12))])
+def test_batch_dealt_to_the_xcds(kernel, tile):
+    """Uneven replicas (more and fewer than the eight XCDs, so that the dealt
+    lists are padded): each equals the lone handle."""
+    lbf = require_gpu()
+    for Ls in ([8, 24, 4, 12, 40, 8, 16, 4, 20, 12, 8], [4, 36, 8]):
+        prms = [dict(PRM, a=0.01 * k, sample_every=3) for k in range(len(Ls))]
+        bat = lbf.Sim.batch(Ls, [50 + k for k in range(len(Ls))], prms)
+        bat.set_plan(kernel, tile)
+        bat.step(7)
+        for r, L in enumerate(Ls):
+            one = lbf.Sim(L, 50 + r, **prms[r])
+            one.set_plan("fused", (32, 8, 7))
+            one.step(7)
+            assert np.array_equal(bat.fields(r, f=True)["f"], one.fields(f=True)["f"]), (Ls, r)
+            assert bat.moments(r)["levels"] == one.moments()["levels"], (Ls, r)
+
+
 def test_default_plans_by_size():
     lbf = require_gpu()
     S, F, R = lbf.LB_KERNEL_SPLIT, lbf.LB_KERNEL_FUSED, lbf.LB_KERNEL_ROWS
