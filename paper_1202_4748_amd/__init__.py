@@ -234,6 +234,7 @@ class Sim:
             self._h = h
             self.Ls = [int(L)]
             self._hb = [int(params.get("hist_bins", 0))]
+            self._cap = [int(params.get("series_capacity", 0))]
         if self._torch:
             import torch
             cs = torch.cuda.current_stream().cuda_stream
@@ -252,6 +253,7 @@ class Sim:
         _check(L_.lb_create_batch(n, arrL, arrP, arrS, ctypes.byref(h)), "lb_create_batch")
         sim = cls(_handle=h, _Ls=Ls)
         sim._hb = [int(p.get("hist_bins", 0)) for p in params_list]
+        sim._cap = [int(p.get("series_capacity", 0)) for p in params_list]
         return sim
 
     def __del__(self):
@@ -299,13 +301,13 @@ class Sim:
         L = self.Ls[replica]
         nk = max(L // 2 - 1, 0)
         sk = np.zeros(3 * max(nk, 1))
-        # first call learns the series size
-        _check(lib().lb_moments(self._h, replica, ctypes.byref(m), _dp(sk), None), "lb_moments")
+        # room for a full ring of the longest record, a level per halving of L
+        record = 5 + 7 * ((L & -L).bit_length() - 1)
+        buf = np.zeros(self._cap[replica] * record) if series and self._cap[replica] else None
+        _check(lib().lb_moments(self._h, replica, ctypes.byref(m), _dp(sk), _dp(buf)), "lb_moments")
         ser = None
-        if series and m.series_len > 0:
-            buf = np.zeros(m.series_len * m.series_record)
-            _check(lib().lb_moments(self._h, replica, ctypes.byref(m), _dp(sk), _dp(buf)), "lb_moments")
-            ser = buf.reshape(m.series_len, m.series_record)
+        if buf is not None and m.series_len > 0:
+            ser = buf[:m.series_len * m.series_record].reshape(m.series_len, m.series_record)
         levels = []
         for i in range(m.n_levels):
             lv = m.level[i]

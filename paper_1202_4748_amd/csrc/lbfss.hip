@@ -111,6 +111,7 @@ struct lb_sim {
     double *d_parts = nullptr;
     float *d_snap = nullptr;
     double *d_ws = nullptr;
+    double *d_report = nullptr;
     double *d_acc = nullptr;
     double *d_series = nullptr;
     int64_t *d_nsamp = nullptr;
@@ -329,25 +330,6 @@ void launch_snapshot(lb_sim *s, int cur) {
                        s->total_sites, (const T *)s->pop[cur], s->d_snap);
 }
 
-// Reduction stages over the snapshot, shared by sampling and by lb_moments'
-// current totals.
-void enqueue_reductions(lb_sim *s) {
-    hipLaunchKernelGGL(k_rows, dim3((unsigned)ceil_div(s->n_rows, kBlock / 64)), dim3(kBlock), 0, s->stream,
-                       s->d_sd, s->d_cum_rows, s->nrep, s->total_sites, (const float *)s->d_snap, s->d_ws);
-    hipLaunchKernelGGL(k_cols, dim3((unsigned)ceil_div(s->n_cols, 64)), dim3(kBlock), 0, s->stream,
-                       s->d_sd, s->d_cum_cols, s->nrep, (const float *)s->d_snap, s->d_ws);
-    hipLaunchKernelGGL(k_planes, dim3((unsigned)ceil_div(s->n_planes, kBlock / 64)), dim3(kBlock), 0, s->stream,
-                       s->d_sd, s->d_cum_planes, s->nrep, s->d_ws);
-    hipLaunchKernelGGL(k_totals, dim3((unsigned)s->nrep), dim3(kBlock), 0, s->stream, s->d_sd,
-                       s->d_desc, s->nrep, s->d_ws);
-}
-
-void enqueue_totals(lb_sim *s, int cur) {
-    if (s->storage == LB_FP16) launch_snapshot<__half>(s, cur);
-    else launch_snapshot<float>(s, cur);
-    enqueue_reductions(s);
-}
-
 void enqueue_sk3(lb_sim *s) {
     for (int r = 0; r < s->nrep; ++r) {
         const SampDesc &d = s->hsd[r];
@@ -380,35 +362,43 @@ void enqueue_sk3(lb_sim *s) {
     }
 }
 
-// Sample stages after the snapshot reductions: box sums, level moments and
-// histograms, axis S(k), series record, 3D S(k).  koff places the record's
-// step relative to the device step counter.
-void enqueue_sample_rest(lb_sim *s, int koff, bool sk3) {
-    if (s->n_direct > 0)
-        hipLaunchKernelGGL(k_box_direct, dim3((unsigned)ceil_div(s->n_direct, kBlock)), dim3(kBlock), 0,
-                           s->stream, s->d_sd, s->d_cum_direct, s->nrep, (const float *)s->d_snap, s->d_ws);
-    if (s->n_bx > 0) {
-        hipLaunchKernelGGL(k_box_x, dim3((unsigned)ceil_div(s->n_bx, kBlock)), dim3(kBlock), 0, s->stream,
-                           s->d_sd, s->d_cum_bx, s->nrep, (const float *)s->d_snap, s->d_ws);
-        hipLaunchKernelGGL(k_box_y, dim3((unsigned)ceil_div(s->n_by, kBlock)), dim3(kBlock), 0, s->stream,
-                           s->d_sd, s->d_cum_by, s->nrep, s->d_ws);
-        hipLaunchKernelGGL(k_box_z, dim3((unsigned)ceil_div(s->n_bz, kBlock)), dim3(kBlock), 0, s->stream,
-                           s->d_sd, s->d_cum_bz, s->nrep, s->d_ws);
-    }
-    for (size_t j = 0; j < s->n_coarse.size(); ++j)
-        hipLaunchKernelGGL(k_coarsen_cube, dim3((unsigned)s->n_coarse[j]), dim3(kBlock), 0, s->stream, s->d_sd,
-                           s->d_cum_coarse[j], s->d_coarse_grp[j], s->nrep, s->d_ws);
-    if (s->n_chunks > 0)
-        hipLaunchKernelGGL(k_level_partials, dim3(s->n_chunks), dim3(kBlock), 0, s->stream, s->d_sd, s->d_chunks,
-                           (const float *)s->d_snap, s->d_ws, s->d_parts, s->d_hist);
-    if (s->n_sk > 0)
-        hipLaunchKernelGGL(k_structure_factor, dim3((unsigned)ceil_div(s->n_sk, kBlock / 64)), dim3(kBlock), 0,
-                           s->stream, s->d_sd, s->d_cum_sk, s->nrep, (const double *)s->d_ws, s->d_acc);
-    if (s->max_nlev > 0)
-        hipLaunchKernelGGL(k_level_reduce, dim3((unsigned)(s->nrep * s->max_nlev)), dim3(kBlock), 0, s->stream,
-                           s->d_sd, s->max_nlev, s->d_ws, (const double *)s->d_parts, s->d_acc);
-    hipLaunchKernelGGL(k_finalize, dim3((unsigned)ceil_div(s->nrep, 64)), dim3(64), 0, s->stream, s->d_sd, s->nrep,
-                       (const double *)s->d_ws, s->d_series, s->d_nsamp, (const uint64_t *)s->d_step, koff);
+// The sample stages over the snapshot (see lbfss_sample.hpp): row, column and
+// plane sums, totals, box sums, level moments and histograms, axis S(k),
+// series record, 3D S(k).  koff places the record's step relative to the
+// device step counter.
+void enqueue_sample(lb_sim *s, int koff, bool sk3) {
+    const SampleArgs a{s->d_sd,       s->d_desc,     s->nrep,     std::max(s->max_nlev, 1), s->total_sites, s->d_snap,
+                       s->d_ws,       s->d_parts,    s->d_acc,    s->d_series,              s->d_hist,      s->d_nsamp,
+                       s->d_step,     s->d_chunks,   s->d_cum_rows, s->d_cum_cols,          s->d_cum_planes,
+                       s->d_cum_direct, s->d_cum_bx, s->d_cum_by, s->d_cum_bz,              s->d_cum_sk};
+    auto blocks = [](int64_t n, int64_t per) { return (int)ceil_div(n, per); };
+    const int waves = kBlock / 64;
+    // coarsening launches ride with the launches after the stage that forms
+    // their level: box sums straight from the snapshot are ready after the
+    // first launch, separable ones after the third
+    size_t next = 0;
+    auto coarse = [&](bool ready) { return ready && next < s->n_coarse.size() ? (int)next++ : -1; };
+    auto n_of = [&](int j) { return j < 0 ? 0 : (int)s->n_coarse[j]; };
+    auto cum_of = [&](int j) { return j < 0 ? (const int64_t *)nullptr : (const int64_t *)s->d_cum_coarse[j]; };
+    auto grp_of = [&](int j) { return j < 0 ? (const CoarsenGroup *)nullptr : (const CoarsenGroup *)s->d_coarse_grp[j]; };
+
+    const int n_rows = blocks(s->n_rows, waves), n_cols = blocks(s->n_cols, 64),
+              n_direct = blocks(s->n_direct, kBlock), n_bx = blocks(s->n_bx, kBlock);
+    hipLaunchKernelGGL(k_sample_a, dim3(n_rows + n_cols + n_direct + n_bx), dim3(kBlock), 0, s->stream, a, n_rows,
+                       n_cols, n_direct);
+    const int n_planes = blocks(s->n_planes, waves), n_by = blocks(s->n_by, kBlock);
+    int j = coarse(n_bx == 0);
+    hipLaunchKernelGGL(k_sample_b, dim3(n_planes + n_by + n_of(j)), dim3(kBlock), 0, s->stream, a, n_planes, n_by,
+                       cum_of(j), grp_of(j));
+    const int n_bz = blocks(s->n_bz, kBlock);
+    j = coarse(n_bx == 0);
+    hipLaunchKernelGGL(k_sample_c, dim3(s->nrep + n_bz + n_of(j)), dim3(kBlock), 0, s->stream, a, s->nrep, n_bz,
+                       cum_of(j), grp_of(j));
+    while ((j = coarse(true)) >= 0)
+        hipLaunchKernelGGL(k_sample_c, dim3(n_of(j)), dim3(kBlock), 0, s->stream, a, 0, 0, cum_of(j), grp_of(j));
+    const int n_sk = blocks(s->n_sk, waves);
+    hipLaunchKernelGGL(k_sample_d, dim3(s->n_chunks + n_sk + 1), dim3(kBlock), 0, s->stream, a, s->n_chunks, n_sk);
+    hipLaunchKernelGGL(k_sample_e, dim3((unsigned)(s->nrep * a.max_nlev)), dim3(kBlock), 0, s->stream, a, koff);
     if (sk3) enqueue_sk3(s);
 }
 
@@ -420,8 +410,9 @@ bool sk3_at(const lb_sim *s, int64_t t) {
 // Take a pending sample of the current state with its own snapshot pass.
 void flush_pending(lb_sim *s) {
     if (!s->pending) return;
-    enqueue_totals(s, (int)(s->t & 1));
-    enqueue_sample_rest(s, 0, sk3_at(s, s->t));
+    if (s->storage == LB_FP16) launch_snapshot<__half>(s, (int)(s->t & 1));
+    else launch_snapshot<float>(s, (int)(s->t & 1));
+    enqueue_sample(s, 0, sk3_at(s, s->t));
     s->pending = false;
 }
 
@@ -467,10 +458,7 @@ int build_graph(lb_sim *s, int G, bool start_pending) {
     for (int k = 0; k < G; ++k) {
         const bool snap = sampling(s) && (k == 0 ? start_pending : k % s->sample_every == 0);
         enqueue_step(s, k & 1, k, snap ? s->d_snap : nullptr);
-        if (snap) {
-            enqueue_reductions(s);
-            enqueue_sample_rest(s, k, sk3_at(s, k));
-        }
+        if (snap) enqueue_sample(s, k, sk3_at(s, k));
     }
     hipLaunchKernelGGL(k_add_step, dim3(1), dim3(1), 0, s->cap_stream, s->d_step, (int64_t)G);
     hipGraph_t graph = nullptr;
@@ -488,7 +476,7 @@ int build_graph(lb_sim *s, int G, bool start_pending) {
 }
 
 int build_sampling(lb_sim *s) {
-    int64_t ws_len = 0, acc_len = 0, ser_len = 0, hist_len = 0;
+    int64_t ws_len = 0, acc_len = 0, ser_len = 0, hist_len = 0, report_len = 0;
     std::vector<BoxChunk> chunks;
     std::vector<int64_t> cum_rows{0}, cum_cols{0}, cum_bx{0}, cum_by{0}, cum_bz{0}, cum_planes{0}, cum_direct{0},
         cum_sk{0};
@@ -556,8 +544,8 @@ int build_sampling(lb_sim *s) {
             d.chunk_count[l] = cnt;
         }
         d.glob_off = ws_len; ws_len += 8;
-        d.levtot_off = ws_len; ws_len += (int64_t)kMoments * std::max(d.nlev, 1);
         d.acc_off = acc_len; acc_len += (int64_t)kMoments * d.nlev + 3 * d.n_k;
+        report_len = std::max(report_len, kReportHead + (int64_t)kMoments * d.nlev + 3 * d.n_k);
         d.hist_bins = s->P[r].hist_bins;
         if (d.hist_bins > 0) {
             d.hist_h = s->P[r].hist_range;
@@ -628,7 +616,9 @@ int build_sampling(lb_sim *s) {
     s->n_chunks = (int)chunks.size();
     s->d_parts = (double *)dev_alloc(s, sizeof(double) * kMoments * std::max<int64_t>(parts_rows, 1));
     s->d_snap = (float *)dev_alloc(s, sizeof(float) * 4 * s->total_sites);
-    s->d_ws = (double *)dev_alloc(s, sizeof(double) * ws_len);
+    // the report of lb_moments sits behind the sampling workspace
+    s->d_ws = (double *)dev_alloc(s, sizeof(double) * (ws_len + report_len));
+    s->d_report = s->d_ws + ws_len;
     s->d_acc = (double *)dev_alloc(s, sizeof(double) * std::max<int64_t>(acc_len, 1));
     s->d_series = (double *)dev_alloc(s, sizeof(double) * std::max<int64_t>(ser_len, 1));
     s->d_nsamp = (int64_t *)dev_alloc(s, sizeof(int64_t) * s->nrep);
@@ -995,8 +985,7 @@ int lb_step(lb_sim *s, int64_t n) {
         const bool snap = s->pending;
         enqueue_step(s, cur, (int)ahead, snap ? s->d_snap : nullptr);
         if (snap) {  // the sample of the state this step started from
-            enqueue_reductions(s);
-            enqueue_sample_rest(s, (int)ahead, sk3_at(s, s->t));
+            enqueue_sample(s, (int)ahead, sk3_at(s, s->t));
             s->pending = false;
         }
         if (++ahead == kMaxStepsAhead) advance();
@@ -1017,17 +1006,28 @@ int lb_sync(lb_sim *s) {
 int lb_moments(lb_sim *s, int replica, lb_moments_t *out, double *sk, double *series) {
     if (!s || !out || replica < 0 || replica >= s->nrep) return LB_EINVAL;
     flush_pending(s);
-    enqueue_totals(s, (int)(s->t & 1));
-    HIPCHK(hipGetLastError());
     const SampDesc &d = s->hsd[replica];
-    std::vector<double> acc((size_t)kMoments * d.nlev + 3 * d.n_k);
-    double gl[8];
-    int64_t ns = 0;
-    HIPCHK(hipMemcpyAsync(acc.data(), s->d_acc + d.acc_off, sizeof(double) * acc.size(), hipMemcpyDeviceToHost,
-                          s->stream));
-    HIPCHK(hipMemcpyAsync(gl, s->d_ws + d.glob_off, sizeof(double) * 8, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(hipMemcpyAsync(&ns, s->d_nsamp + replica, sizeof(int64_t), hipMemcpyDeviceToHost, s->stream));
+    const RepDesc &rd = s->hdesc[replica];
+    const int cur = (int)(s->t & 1);
+    const unsigned nrows = (unsigned)ceil_div((int64_t)d.L * d.L, kBlock / 64);
+    if (s->storage == LB_FP16)
+        hipLaunchKernelGGL(k_state_rows<__half>, dim3(nrows), dim3(kBlock), 0, s->stream, rd,
+                           (const __half *)s->pop[cur] + Q * rd.site_off, s->d_ws + d.rows_off);
+    else
+        hipLaunchKernelGGL(k_state_rows<float>, dim3(nrows), dim3(kBlock), 0, s->stream, rd,
+                           (const float *)s->pop[cur] + Q * rd.site_off, s->d_ws + d.rows_off);
+    hipLaunchKernelGGL(k_state_planes, dim3((unsigned)ceil_div(4 * d.L, kBlock / 64)), dim3(kBlock), 0, s->stream,
+                       s->d_sd, replica, s->d_ws);
+    hipLaunchKernelGGL(k_state_report, dim3(1), dim3(kBlock), 0, s->stream, s->d_sd, s->d_desc, replica, s->d_ws,
+                       (const double *)s->d_acc, (const int64_t *)s->d_nsamp, (const int *)s->d_err, s->d_report);
+    HIPCHK(hipGetLastError());
+    std::vector<double> rep((size_t)kReportHead + kMoments * d.nlev + 3 * d.n_k);
+    HIPCHK(hipMemcpyAsync(rep.data(), s->d_report, sizeof(double) * rep.size(), hipMemcpyDeviceToHost, s->stream));
     HIPCHK(hipStreamSynchronize(s->stream));
+    const double *gl = rep.data(), *acc = gl + kReportHead;
+    int64_t ns = 0, err = 0;
+    std::memcpy(&ns, gl + 8, sizeof(ns));
+    std::memcpy(&err, gl + 9, sizeof(err));
     std::memset(out, 0, sizeof(*out));
     out->step = s->t;
     out->n_samples = ns;
@@ -1045,7 +1045,7 @@ int lb_moments(lb_sim *s, int replica, lb_moments_t *out, double *sk, double *se
         const int64_t nbl = d.L / d.lev_L[l];
         ls.Lb = d.lev_L[l];
         ls.n_boxes = nbl * nbl * nbl;
-        const double *a = acc.data() + (size_t)l * kMoments;
+        const double *a = acc + (size_t)l * kMoments;
         ls.sum_m = a[0];
         ls.sum_m2 = a[1];
         ls.sum_m3 = a[2];
@@ -1054,7 +1054,7 @@ int lb_moments(lb_sim *s, int replica, lb_moments_t *out, double *sk, double *se
         ls.sum_E = a[5];
         ls.sum_E2 = a[6];
     }
-    if (sk) std::memcpy(sk, acc.data() + (size_t)kMoments * d.nlev, sizeof(double) * 3 * d.n_k);
+    if (sk) std::memcpy(sk, acc + (size_t)kMoments * d.nlev, sizeof(double) * 3 * d.n_k);
     if (series && out->series_len > 0) {
         std::vector<double> ring((size_t)d.series_cap * d.rec_len);
         HIPCHK(hipMemcpyAsync(ring.data(), s->d_series + d.series_off, sizeof(double) * ring.size(),
@@ -1066,7 +1066,7 @@ int lb_moments(lb_sim *s, int replica, lb_moments_t *out, double *sk, double *se
             std::memcpy(series + i * d.rec_len, ring.data() + slot * d.rec_len, sizeof(double) * d.rec_len);
         }
     }
-    return check_err(s);
+    return err ? LB_EUNSTABLE : LB_OK;
 }
 
 int lb_histogram(lb_sim *s, int replica, uint64_t *counts) {
