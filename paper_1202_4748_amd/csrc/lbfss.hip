@@ -1603,8 +1603,10 @@ struct lb2_sim {
     float *pop[2] = {nullptr, nullptr};  // [replica][9][L^2]
     float *d_drho = nullptr;
     int *d_err = nullptr;
-    double *d_twid = nullptr, *d_snap = nullptr, *d_acc = nullptr;  // per replica [3][L^2], [5][L^2]
-    double2 *d_X = nullptr;                                         // per replica [3][L^2]
+    double2 *d_twid = nullptr;  // e^{-2 pi i k / L}
+    double *d_acc = nullptr;    // per replica k2_acc_len(L)
+    double2 *d_X = nullptr;     // per replica [3][L][L/2 + 1]; the full spectra of one while they are read
+    K2SpecPlan spec{};
     int64_t t = 0, n_samples = 0;
 };
 
@@ -1674,22 +1676,21 @@ int lb2_create_batch(int n, int L, const lb2_params *p, const uint64_t *seeds, l
         if (!(s->pop[b] = (float *)dev_alloc2(s, sizeof(float) * Q2 * N * n))) return fail(LB_ENOMEM);
     s->d_drho = (float *)dev_alloc2(s, sizeof(float) * N);
     s->d_err = (int *)dev_alloc2(s, sizeof(int));
-    s->d_twid = (double *)dev_alloc2(s, sizeof(double) * 2 * L);
+    s->d_twid = (double2 *)dev_alloc2(s, sizeof(double2) * L);
     s->d_desc = (D2Desc *)dev_alloc2(s, sizeof(D2Desc) * n);
     if (!s->d_drho || !s->d_err || !s->d_twid || !s->d_desc) return fail(LB_ENOMEM);
     if (s->sample_every > 0) {
-        s->d_snap = (double *)dev_alloc2(s, sizeof(double) * 3 * N * n);
-        s->d_X = (double2 *)dev_alloc2(s, sizeof(double2) * 3 * N * n);
-        s->d_acc = (double *)dev_alloc2(s, sizeof(double) * 5 * N * n);
-        if (!s->d_snap || !s->d_X || !s->d_acc) return fail(LB_ENOMEM);
-        if (hipMemsetAsync(s->d_acc, 0, sizeof(double) * 5 * N * n, s->stream) != hipSuccess) return fail(LB_EDEVICE);
+        const size_t xlen = std::max(sizeof(double2) * 3 * L * (L / 2 + 1) * n, sizeof(double) * 5 * N);
+        s->d_X = (double2 *)dev_alloc2(s, xlen);
+        s->d_acc = (double *)dev_alloc2(s, sizeof(double) * k2_acc_len(L) * n);
+        if (!s->d_X || !s->d_acc) return fail(LB_ENOMEM);
+        if (hipMemsetAsync(s->d_acc, 0, sizeof(double) * k2_acc_len(L) * n, s->stream) != hipSuccess)
+            return fail(LB_EDEVICE);
+        s->spec = k2_spec_plan(L, n);
     }
-    std::vector<double> tw(2 * L);
-    for (int k = 0; k < L; ++k) {
-        tw[k] = std::cos(2.0 * M_PI * k / L);
-        tw[L + k] = std::sin(2.0 * M_PI * k / L);
-    }
-    if (hipMemcpyAsync(s->d_twid, tw.data(), sizeof(double) * 2 * L, hipMemcpyHostToDevice, s->stream) != hipSuccess ||
+    std::vector<double2> tw(L);
+    for (int k = 0; k < L; ++k) tw[k] = make_double2(std::cos(2.0 * M_PI * k / L), -std::sin(2.0 * M_PI * k / L));
+    if (hipMemcpyAsync(s->d_twid, tw.data(), sizeof(double2) * L, hipMemcpyHostToDevice, s->stream) != hipSuccess ||
         hipMemcpyAsync(s->d_desc, s->D.data(), sizeof(D2Desc) * n, hipMemcpyHostToDevice, s->stream) != hipSuccess ||
         hipMemsetAsync(s->d_err, 0, sizeof(int), s->stream) != hipSuccess)
         return fail(LB_EDEVICE);
@@ -1721,8 +1722,6 @@ int check2(lb2_sim *s) {
 
 int lb2_step(lb2_sim *s, int64_t n) {
     if (!s || n < 0) return LB_EINVAL;
-    const int64_t N = (int64_t)s->L * s->L;
-    const unsigned nb = (unsigned)ceil_div(N, kBlock);
     const int tiles = (int)(ceil_div(s->L, K2TX) * ceil_div(s->L, K2TY));
     const unsigned R = (unsigned)s->nrep;
     for (int64_t k = 0; k < n; ++k) {
@@ -1732,57 +1731,7 @@ int lb2_step(lb2_sim *s, int64_t n) {
                            (const float *)s->pop[cur], s->pop[cur ^ 1], (uint64_t)s->t, s->d_err);
         s->t += 1;
         if (s->sample_every > 0 && s->t % s->sample_every == 0) {
-            const unsigned lines = (unsigned)(3 * s->L);
-            const bool pow2 = (s->L & (s->L - 1)) == 0;
-            int logL = 0;
-            while ((1 << logL) < s->L) ++logL;
-            // power-of-two L <= 1024: the density and momentum formed straight
-            // into the row transforms (no snapshot array), three lines per
-            // workgroup; the columns of a batch four adjacent kx per workgroup
-            // (L <= 256) with the spectra added in the same pass, those of one
-            // lattice one line per workgroup (three times the workgroups for
-            // its latency), then the spectra
-            if (pow2 && s->L <= kK2LinesMaxL) {
-                const bool small = s->L <= 256;  // LDS lines sized for L = 256
-                hipLaunchKernelGGL(small ? k2_snap_fft_rows<256> : k2_snap_fft_rows<kK2LinesMaxL>,
-                                   dim3((unsigned)s->L, R), dim3(kBlock), 0, s->stream, s->L, logL,
-                                   (const float *)s->pop[cur ^ 1], (const double *)s->d_twid, s->d_X);
-                if (s->nrep == 1) {
-                    hipLaunchKernelGGL(k2_fft_cols<1>, dim3(lines, R), dim3(kBlock), 0, s->stream, s->L, logL,
-                                       s->d_X, (const double *)s->d_twid);
-                    hipLaunchKernelGGL(k2_spec_acc, dim3(nb, R), dim3(kBlock), 0, s->stream, s->L,
-                                       (const double2 *)s->d_X, s->d_acc);
-                } else if (small) {
-                    hipLaunchKernelGGL((k2_fft_cols3_acc<256, 4>), dim3((unsigned)s->L / 4, R), dim3(kBlock), 0,
-                                       s->stream, s->L, logL, (const double2 *)s->d_X, (const double *)s->d_twid,
-                                       s->d_acc);
-                } else {
-                    hipLaunchKernelGGL((k2_fft_cols3_acc<kK2LinesMaxL, 1>), dim3((unsigned)s->L, R), dim3(kBlock), 0,
-                                       s->stream, s->L, logL, (const double2 *)s->d_X, (const double *)s->d_twid,
-                                       s->d_acc);
-                }
-                s->n_samples += 1;
-                continue;
-            }
-            hipLaunchKernelGGL(k2_snap, dim3(nb, R), dim3(kBlock), 0, s->stream, s->L, (const float *)s->pop[cur ^ 1],
-                               s->d_snap);
-            if (pow2) {  // FFTs
-                hipLaunchKernelGGL(k2_fft_rows, dim3(lines, R), dim3(kBlock), 0, s->stream, s->L, logL,
-                                   (const double *)s->d_snap, (const double *)s->d_twid, s->d_X);
-                // L = 2048 (the only power of two left here): two adjacent
-                // columns per workgroup (rows read as 32 bytes; 64 KB of LDS,
-                // two workgroups per CU): 6% faster whole steps than one, four
-                // (one workgroup per CU) 4%
-                hipLaunchKernelGGL(k2_fft_cols<2>, dim3(lines / 2, R), dim3(kBlock), 0, s->stream, s->L, logL,
-                                   s->d_X, (const double *)s->d_twid);
-                hipLaunchKernelGGL(k2_spec_acc, dim3(nb, R), dim3(kBlock), 0, s->stream, s->L, (const double2 *)s->d_X,
-                                   s->d_acc);
-            } else {
-                hipLaunchKernelGGL(k2_dft_rows, dim3(lines, R), dim3(kBlock), 0, s->stream, s->L,
-                                   (const double *)s->d_snap, (const double *)s->d_twid, s->d_X);
-                hipLaunchKernelGGL(k2_dft_cols, dim3(nb, R), dim3(kBlock), 0, s->stream, s->L,
-                                   (const double2 *)s->d_X, (const double *)s->d_twid, s->d_acc);
-            }
+            launch_k2_spectra(s->spec, s->L, s->nrep, s->pop[cur ^ 1], s->d_twid, s->d_X, s->d_acc, s->stream);
             s->n_samples += 1;
         }
     }
@@ -1849,7 +1798,12 @@ int lb2_spectra(lb2_sim *s, int replica, int64_t *n_samples, double *S, double *
     if (!s || !n_samples || replica < 0 || replica >= s->nrep) return LB_EINVAL;
     if (s->sample_every <= 0) return LB_ESTATE;
     const int64_t N = (int64_t)s->L * s->L;
-    const double *acc = s->d_acc + (int64_t)replica * 5 * N;
+    const int L = s->L;
+    const unsigned nt = (unsigned)ceil_div(L, 32);
+    double *acc = (double *)s->d_X;
+    hipLaunchKernelGGL(k2_spec_full, dim3(nt, nt, 5), dim3(kBlock), 0, s->stream, L,
+                       (const double *)s->d_acc + (int64_t)replica * k2_acc_len(L), acc);
+    if (hipGetLastError() != hipSuccess) return LB_EDEVICE;
     double *dst[5] = {S, Jx, Jy, Jpar, Jperp};
     for (int c = 0; c < 5; ++c)
         if (dst[c] && hipMemcpyAsync(dst[c], acc + c * N, sizeof(double) * N, hipMemcpyDeviceToHost, s->stream) !=
@@ -1863,8 +1817,8 @@ int lb2_spectra(lb2_sim *s, int replica, int64_t *n_samples, double *S, double *
 int lb2_reset_spectra(lb2_sim *s) {
     if (!s) return LB_EINVAL;
     if (s->sample_every <= 0) return LB_ESTATE;
-    const int64_t N = (int64_t)s->L * s->L;
-    if (hipMemsetAsync(s->d_acc, 0, sizeof(double) * 5 * N * s->nrep, s->stream) != hipSuccess) return LB_EDEVICE;
+    if (hipMemsetAsync(s->d_acc, 0, sizeof(double) * k2_acc_len(s->L) * s->nrep, s->stream) != hipSuccess)
+        return LB_EDEVICE;
     s->n_samples = 0;
     return LB_OK;
 }

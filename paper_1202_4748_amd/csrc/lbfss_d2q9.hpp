@@ -15,6 +15,9 @@
 // 5 (1,1) 6 (-1,-1) 7 (1,-1) 8 (-1,1).
 #pragma once
 
+#include <algorithm>
+
+#include "lbfss_fft.hpp"
 #include "lbfss_fused.hpp"
 
 namespace lbfss {
@@ -355,308 +358,237 @@ k2_import(D2Desc D, const double *__restrict__ f, float *__restrict__ pop) {
     }
 }
 
-// Sampling: density deviation and momentum of the state, FP64 [3][L^2].
-// (The sampling kernels take replica blockIdx.y of a batch.)
-__global__ void __launch_bounds__(kBlock)
-k2_snap(int L, const float *__restrict__ pop_all, double *__restrict__ out_all) {
+// ---------------------------------------------------------------------------
+// Sampling: the spectra of density and momentum.  The fields are real, so
+// their transforms are kept for kx = 0..L/2 only (Lh columns); the other modes
+// are mirrored when the spectra are read.
+//   k2_spec_rows   a few rows a workgroup: density and momentum summed straight
+//                  from the pulled populations, the row transforms (even L: the
+//                  even and odd sites of a row as the real and imaginary part
+//                  of a line of L/2 points), X[3][y][kx]
+//   k2_spec_cols   a few columns a workgroup: the column transforms, the
+//                  spectra added to the accumulators [5][kx][ky]
+// Per sample, against transforms of all columns (powers of two) or direct ones
+// (other L): 64 replicas of 256^2 400 -> 196 us, 2048^2 497 -> 300, 256^2
+// 23 -> 16, 376^2 310 -> 37, 32 replicas of 200^2 1190 -> 57.  Large launches
+// are bound by LDS round trips and by memory in about equal parts (2048^2:
+// 521 MB a sample at 1.7 TB/s), one lattice of 256^2 by the chain of passes.
+// ---------------------------------------------------------------------------
+constexpr int kTwLds = 512;  // longest twiddle table copied to LDS
+
+// Accumulators of one replica: [5][Lh][L] spectra S, J_x, J_y, J_par, J_perp
+// of mode (kx, ky), then [2][Lh] J_par, J_perp of the modes (-kx, L/2) of even
+// L: the direction of k folds L/2 to +L/2 on both sides, so they are not the
+// mirror images of (kx, L/2).
+__host__ __device__ constexpr int64_t k2_acc_len(int L) { return (int64_t)5 * (L / 2 + 1) * L + 2 * (L / 2 + 1); }
+
+template <int NT, int U>
+__global__ void __launch_bounds__(NT)
+k2_spec_rows(int L, FftPlan p, int rows, const float *__restrict__ pop_all, const double2 *__restrict__ tw,
+             double2 *__restrict__ X_all) {
+    __shared__ double2 S[U * NT + U * NT / 8 + 64];
+    __shared__ double2 s_tw[NT <= kTwLds ? kTwLds : 1];
     const int64_t N = (int64_t)L * L;
+    const int Lh = L / 2 + 1, n = p.n, stride = fft_stride(n), y0 = blockIdx.x * rows;
     const float *pop = pop_all + (int64_t)blockIdx.y * Q2 * N;
-    double *out = out_all + (int64_t)blockIdx.y * 3 * N;
-    const int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (s >= N) return;
-    const int x = (int)(s % L), y = (int)(s / L);
-    double r = 0.0, jx = 0.0, jy = 0.0;
+    double2 *X = X_all + (int64_t)blockIdx.y * 3 * L * Lh;
+    const bool even = L % 2 == 0, in_lds = NT <= kTwLds && L <= kTwLds;
+    if (in_lds)
+        for (int k = threadIdx.x; k < L; k += NT) s_tw[k] = tw[k];
+    const float r_L = 1.0f / (float)L, r_Lh = 1.0f / (float)Lh;
+    for (int i = threadIdx.x; i < rows * L; i += NT) {
+        const int row = div_small(i, r_L), x = i - row * L, y = y0 + row;
+        double v[3] = {0.0, 0.0, 0.0};
+        if (y < L) {
+            float d[Q2];
+            pull2(pop, L, x, y, d);
 #pragma unroll
-    for (int i = 0; i < Q2; ++i) {
-        const int xs = wrap2(x - c2x(i), L), ys = wrap2(y - c2y(i), L);
-        const double v = (double)pop[i * N + xs + (int64_t)L * ys];
-        r += v;
-        jx += c2x(i) * v;
-        jy += c2y(i) * v;
-    }
-    out[s] = r;
-    out[N + s] = jx;
-    out[2 * N + s] = jy;
-}
-
-// Row transforms X_c[y][kx] = sum_x v_c[y][x] e^{-2 pi i kx x / L}: one
-// workgroup per (channel, row), twiddles cos, sin of 2 pi k / L.
-__global__ void __launch_bounds__(kBlock)
-k2_dft_rows(int L, const double *__restrict__ v_all, const double *__restrict__ twid, double2 *__restrict__ X_all) {
-    __shared__ double row[2048], cs[2048], sn[2048];
-    const double *v = v_all + (int64_t)blockIdx.y * 3 * L * L;
-    double2 *X = X_all + (int64_t)blockIdx.y * 3 * L * L;
-    const int64_t r = blockIdx.x;  // channel * L + y
-    for (int x = threadIdx.x; x < L; x += kBlock) {
-        row[x] = v[r * L + x];
-        cs[x] = twid[x];
-        sn[x] = twid[L + x];
-    }
-    __syncthreads();
-    for (int kx = threadIdx.x; kx < L; kx += kBlock) {
-        double re = 0.0, im = 0.0;
-        int k = 0;
-        for (int x = 0; x < L; ++x) {
-            re += row[x] * cs[k];
-            im -= row[x] * sn[k];
-            k += kx;
-            if (k >= L) k -= L;
-        }
-        X[r * L + kx] = make_double2(re, im);
-    }
-}
-
-// Column transforms and accumulation, one thread per (ky, kx): per sample
-// S += |rho_k|^2 / N, Jx, Jy += |j_a,k|^2 / N, and the projections of j_k on
-// k (longitudinal) and across it (transverse); k = 0 has no direction (0).
-__global__ void __launch_bounds__(kBlock)
-k2_dft_cols(int L, const double2 *__restrict__ X_all, const double *__restrict__ twid, double *__restrict__ acc_all) {
-    const int64_t N = (int64_t)L * L;
-    const double2 *X = X_all + (int64_t)blockIdx.y * 3 * N;
-    double *acc = acc_all + (int64_t)blockIdx.y * 5 * N;
-    const int64_t o = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (o >= N) return;
-    const int ky = (int)(o / L), kx = (int)(o - (int64_t)ky * L);
-    double re[3] = {0, 0, 0}, im[3] = {0, 0, 0};
-    int k = 0;
-    for (int y = 0; y < L; ++y) {
-        const double c = twid[k], sn = twid[L + k];
-#pragma unroll
-        for (int ch = 0; ch < 3; ++ch) {
-            const double2 v = X[(int64_t)ch * N + (int64_t)y * L + kx];
-            re[ch] += v.x * c + v.y * sn;
-            im[ch] += v.y * c - v.x * sn;
-        }
-        k += ky;
-        if (k >= L) k -= L;
-    }
-    const double inv = 1.0 / (double)N;
-    const int mx = kx <= L / 2 ? kx : kx - L, my = ky <= L / 2 ? ky : ky - L;
-    const double kn = sqrt((double)mx * mx + (double)my * my);
-    const double hx = kn > 0 ? mx / kn : 0.0, hy = kn > 0 ? my / kn : 0.0;
-    const double pr = hx * re[1] + hy * re[2], pi = hx * im[1] + hy * im[2];
-    const double tr = -hy * re[1] + hx * re[2], ti = -hy * im[1] + hx * im[2];
-    acc[o] += (re[0] * re[0] + im[0] * im[0]) * inv;
-    acc[N + o] += (re[1] * re[1] + im[1] * im[1]) * inv;
-    acc[2 * N + o] += (re[2] * re[2] + im[2] * im[2]) * inv;
-    acc[3 * N + o] += (pr * pr + pi * pi) * inv;
-    acc[4 * N + o] += (tr * tr + ti * ti) * inv;
-}
-
-// Power-of-two L: the same transforms as radix-2 FFTs, O(L^2 log L) per
-// sample instead of O(L^3).  One line of L complex values in LDS, loaded in
-// bit-reversed order, then the log2 L butterfly stages of length len = 2,
-// 4, ..., L with the twiddles e^{-2 pi i k / L} (k = j L / len).  Up to three
-// consecutive stages run together on groups of 2^M values held in registers:
-// each value goes through the same butterflies, with the same twiddles, as
-// in separate stages, with a barrier and an LDS round trip per pass instead
-// of per stage.
-__device__ __forceinline__ void k2_bfly(double2 &u, double2 &v, double c, double sn) {
-    const double tr = v.x * c + v.y * sn, ti = v.y * c - v.x * sn;  // v e^{-i theta}
-    v = make_double2(u.x - tr, u.y - ti);
-    u = make_double2(u.x + tr, u.y + ti);
-}
-
-// Stages len, 2 len, ..., 2^(M-1) len on NL lines (line l at buf + l * stride):
-// group g holds the values e_t = base + t half (half = len / 2, t < 2^M), and
-// stage k pairs e_t with e_(t + 2^k) (bit k of t clear) at twiddle
-// (j + (t mod 2^k) half) L / (2^k len), j = g mod half.
-template <int NL, int M>
-__device__ __forceinline__ void k2_fft_pass(double2 *buf, int stride, int L, int len,
-                                            const double *__restrict__ twid) {
-    constexpr int G = 1 << M;
-    const int half = len >> 1, ng = L >> M;
-    for (int b = threadIdx.x; b < NL * ng; b += kBlock) {
-        const int line = b / ng, g = b - line * ng;
-        const int grp = g / half, j = g - grp * half;
-        double2 *ln = buf + line * stride + grp * (half << M) + j;
-        double2 e[G];
-#pragma unroll
-        for (int t = 0; t < G; ++t) e[t] = ln[t * half];
-#pragma unroll
-        for (int k = 0; k < M; ++k) {
-            const int st = L / (len << k);
-#pragma unroll
-            for (int t = 0; t < G; ++t) {
-                if ((t >> k) & 1) continue;
-                const int tw = (j + (t & ((1 << k) - 1)) * half) * st;
-                k2_bfly(e[t], e[t + (1 << k)], twid[tw], twid[L + tw]);
+            for (int q = 0; q < Q2; ++q) {
+                v[0] += (double)d[q];
+                v[1] += c2x(q) * (double)d[q];
+                v[2] += c2y(q) * (double)d[q];
             }
         }
 #pragma unroll
-        for (int t = 0; t < G; ++t) ln[t * half] = e[t];
-    }
-    __syncthreads();
-}
-
-// NL lines of L values side by side (line l at buf + l * stride), one
-// barrier per pass for all of them.  Three stages per pass where the groups
-// of eight still give every thread one (2048-point lines, the batches'
-// twelve-line column passes), else two (a single 256-point line: 32 groups
-// of eight would leave seven threads in eight idle).
-template <int NL>
-__device__ __forceinline__ void k2_fft_lines(double2 *buf, int stride, int L, const double *__restrict__ twid) {
-    int len = 2, left = __builtin_ctz((unsigned)L);
-    if (NL * L >= 8 * kBlock)
-        for (; left >= 3; left -= 3, len <<= 3) k2_fft_pass<NL, 3>(buf, stride, L, len, twid);
-    for (; left >= 2; left -= 2, len <<= 2) k2_fft_pass<NL, 2>(buf, stride, L, len, twid);
-    if (left == 1) k2_fft_pass<NL, 1>(buf, stride, L, len, twid);
-}
-
-__device__ __forceinline__ void k2_fft_line(double2 *buf, int L, const double *__restrict__ twid) {
-    k2_fft_lines<1>(buf, L, L, twid);
-}
-
-// Power-of-two L <= kK2LinesMaxL: the density deviation and momentum of the
-// state (the sums of k2_snap, in its order) formed straight into bit-reversed
-// LDS lines and their three row transforms side by side, one workgroup per
-// (row, replica); k2_fft_cols3_acc then takes the columns.  The same values
-// as k2_snap + k2_fft_rows, without the snapshot array and with a third of
-// the barriers.
-// ML: the largest L of the instance (its LDS lines).
-constexpr int kK2LinesMaxL = 1024;
-template <int ML>
-__global__ void __launch_bounds__(kBlock)
-k2_snap_fft_rows(int L, int logL, const float *__restrict__ pop_all, const double *__restrict__ twid,
-                 double2 *__restrict__ X_all) {
-    __shared__ double2 buf[3 * ML];
-    const int64_t N = (int64_t)L * L;
-    const float *pop = pop_all + (int64_t)blockIdx.y * Q2 * N;
-    double2 *X = X_all + (int64_t)blockIdx.y * 3 * N;
-    const int y = blockIdx.x;
-    for (int x = threadIdx.x; x < L; x += kBlock) {
-        double r = 0.0, jx = 0.0, jy = 0.0;
-#pragma unroll
-        for (int i = 0; i < Q2; ++i) {
-            const int xs = wrap2(x - c2x(i), L), ys = wrap2(y - c2y(i), L);
-            const double v = (double)pop[i * N + xs + (int64_t)L * ys];
-            r += v;
-            jx += c2x(i) * v;
-            jy += c2y(i) * v;
+        for (int c = 0; c < 3; ++c) {
+            double2 *ln = S + (3 * row + c) * stride;
+            if (!even) ln[fft_slot(x)] = make_double2(v[c], 0.0);
+            else if (x & 1) ln[fft_slot(x >> 1)].y = v[c];
+            else ln[fft_slot(x >> 1)].x = v[c];
         }
-        const int br = (int)(__brev((unsigned)x) >> (32 - logL));
-        buf[br] = make_double2(r, 0.0);
-        buf[L + br] = make_double2(jx, 0.0);
-        buf[2 * L + br] = make_double2(jy, 0.0);
     }
     __syncthreads();
-    k2_fft_lines<3>(buf, L, L, twid);
-    for (int kx = threadIdx.x; kx < L; kx += kBlock)
-#pragma unroll
-        for (int ch = 0; ch < 3; ++ch) X[ch * N + (int64_t)y * L + kx] = buf[ch * L + kx];
-}
-
-// Row FFTs X_c[y][kx] of the snapshot: one workgroup per (channel, row).
-__global__ void __launch_bounds__(kBlock)
-k2_fft_rows(int L, int logL, const double *__restrict__ v_all, const double *__restrict__ twid,
-            double2 *__restrict__ X_all) {
-    __shared__ double2 buf[2048];
-    const double *v = v_all + (int64_t)blockIdx.y * 3 * L * L;
-    double2 *X = X_all + (int64_t)blockIdx.y * 3 * L * L;
-    const int64_t r = blockIdx.x;  // channel * L + y
-    for (int x = threadIdx.x; x < L; x += kBlock)
-        buf[__brev((unsigned)x) >> (32 - logL)] = make_double2(v[r * L + x], 0.0);
-    __syncthreads();
-    k2_fft_line(buf, L, twid);
-    for (int kx = threadIdx.x; kx < L; kx += kBlock) X[r * L + kx] = buf[kx];
-}
-
-// Column FFTs in place: X_c[ky][kx] from X_c[y][kx], one workgroup per
-// (channel, CPW adjacent kx; each row read as CPW consecutive values), the
-// butterflies of k2_fft_line on each column.
-template <int CPW>
-__global__ void __launch_bounds__(kBlock)
-k2_fft_cols(int L, int logL, double2 *__restrict__ X_all, const double *__restrict__ twid) {
-    __shared__ double2 buf[CPW * 2048];
-    const int64_t N = (int64_t)L * L;
-    double2 *X = X_all + (int64_t)blockIdx.y * 3 * N;
-    const int per = L / CPW, ch = blockIdx.x / per, kx0 = (blockIdx.x - ch * per) * CPW;
-    double2 *col = X + ch * N + kx0;
-    for (int i = threadIdx.x; i < L * CPW; i += kBlock) {
-        const int y = i / CPW, c = i - y * CPW;
-        buf[c * L + (__brev((unsigned)y) >> (32 - logL))] = col[(int64_t)y * L + c];
-    }
-    __syncthreads();
-    if constexpr (CPW == 1) k2_fft_line(buf, L, twid);
-    else k2_fft_lines<CPW>(buf, L, L, twid);
-    for (int i = threadIdx.x; i < L * CPW; i += kBlock) {
-        const int ky = i / CPW, c = i - ky * CPW;
-        col[(int64_t)ky * L + c] = buf[c * L + ky];
+    const double2 *t = in_lds ? s_tw : tw;
+    fft_lines<NT, U>(S, 3 * rows, p, t);
+    for (int i = threadIdx.x; i < 3 * rows * Lh; i += NT) {
+        const int line = div_small(i, r_Lh), k = i - line * Lh, row = line / 3, c = line - 3 * row, y = y0 + row;
+        if (y >= L) continue;
+        const double2 *ln = S + line * stride;
+        double2 X1;
+        if (even) {  // X_k = E_k + w^k O_k, E and O the transforms of the even and odd sites
+            const double2 a = ln[fft_slot(k == n ? 0 : k)], b = ln[fft_slot(k == 0 ? 0 : n - k)];
+            const double2 E = make_double2(0.5 * (a.x + b.x), 0.5 * (a.y - b.y));
+            const double2 O = make_double2(0.5 * (a.y + b.y), 0.5 * (b.x - a.x));
+            X1 = cadd(E, cmul(O, t[k]));
+        } else {
+            X1 = ln[fft_slot(k)];
+        }
+        X[((int64_t)c * L + y) * Lh + k] = X1;
     }
 }
 
-// The spectra of mode (ky, kx) from its transformed channels (density, jx,
-// jy), added to the accumulators at o = ky L + kx: |rho_k|^2, |jx_k|^2,
-// |jy_k|^2 and the projections of j_k on k (longitudinal) and across it
-// (transverse), each divided by N; k = 0 has no direction (0).
-__device__ __forceinline__ void k2_spec_add(double *acc, int64_t N, int L, int ky, int kx, const double (&re)[3],
-                                            const double (&im)[3]) {
-    const int64_t o = (int64_t)ky * L + kx;
-    const double inv = 1.0 / (double)N;
-    const int mx = kx <= L / 2 ? kx : kx - L, my = ky <= L / 2 ? ky : ky - L;
+// The spectra of mode (kx, ky) from its transformed channels (density, jx,
+// jy): |rho_k|^2, |jx_k|^2, |jy_k|^2 and the projections of j_k on k
+// (longitudinal) and across it (transverse), each divided by N; k = 0 has no
+// direction (0).
+__device__ __forceinline__ void k2_spec_add(double *__restrict__ acc, int L, int ky, int kx, double2 r, double2 jx,
+                                            double2 jy) {
+    const int Lh = L / 2 + 1;
+    const int64_t A = (int64_t)Lh * L, o = (int64_t)kx * L + ky;
+    const double inv = 1.0 / ((double)L * (double)L);
+    const int mx = kx, my = ky <= L / 2 ? ky : ky - L;
     const double kn = sqrt((double)mx * mx + (double)my * my);
     const double hx = kn > 0 ? mx / kn : 0.0, hy = kn > 0 ? my / kn : 0.0;
-    const double pr = hx * re[1] + hy * re[2], pi = hx * im[1] + hy * im[2];
-    const double tr = -hy * re[1] + hx * re[2], ti = -hy * im[1] + hx * im[2];
-    acc[o] += (re[0] * re[0] + im[0] * im[0]) * inv;
-    acc[N + o] += (re[1] * re[1] + im[1] * im[1]) * inv;
-    acc[2 * N + o] += (re[2] * re[2] + im[2] * im[2]) * inv;
-    acc[3 * N + o] += (pr * pr + pi * pi) * inv;
-    acc[4 * N + o] += (tr * tr + ti * ti) * inv;
+    auto norm = [&](double re, double im) { return (re * re + im * im) * inv; };
+    acc[o] += norm(r.x, r.y);
+    acc[A + o] += norm(jx.x, jx.y);
+    acc[2 * A + o] += norm(jy.x, jy.y);
+    acc[3 * A + o] += norm(hx * jx.x + hy * jy.x, hx * jx.y + hy * jy.y);
+    acc[4 * A + o] += norm(-hy * jx.x + hx * jy.x, -hy * jx.y + hx * jy.y);
+    if (2 * ky == L) {  // (-kx, L/2): its j is the conjugate of j at (kx, -L/2) = (kx, L/2)
+        acc[5 * A + kx] += norm(-hx * jx.x + hy * jy.x, -hx * jx.y + hy * jy.y);
+        acc[5 * A + Lh + kx] += norm(hy * jx.x + hx * jy.x, hy * jx.y + hx * jy.y);
+    }
 }
 
-// Accumulation of the spectra from the transformed channels, one thread per
-// (ky, kx): the same sums as the direct transform's.
-__global__ void __launch_bounds__(kBlock)
-k2_spec_acc(int L, const double2 *__restrict__ X_all, double *__restrict__ acc_all) {
-    const int64_t N = (int64_t)L * L;
-    const double2 *X = X_all + (int64_t)blockIdx.y * 3 * N;
-    double *acc = acc_all + (int64_t)blockIdx.y * 5 * N;
-    const int64_t o = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (o >= N) return;
-    const int ky = (int)(o / L), kx = (int)(o - (int64_t)ky * L);
-    double re[3], im[3];
-#pragma unroll
-    for (int ch = 0; ch < 3; ++ch) {
-        const double2 v = X[(int64_t)ch * N + o];
-        re[ch] = v.x;
-        im[ch] = v.y;
-    }
-    k2_spec_add(acc, N, L, ky, kx, re, im);
-}
-
-// Batches: the column transforms of CPW adjacent kx (three channels each,
-// 3 CPW lines side by side; each row read as CPW consecutive values) and the
-// spectra accumulated straight from LDS, without writing the columns back:
-// per line the butterflies of k2_fft_cols, per mode the sums of k2_spec_acc.
-template <int ML, int CPW>
-__global__ void __launch_bounds__(kBlock)
-k2_fft_cols3_acc(int L, int logL, const double2 *__restrict__ X_all, const double *__restrict__ twid,
-                 double *__restrict__ acc_all) {
-    __shared__ double2 buf[3 * CPW * ML];
-    const int64_t N = (int64_t)L * L;
-    const double2 *X = X_all + (int64_t)blockIdx.y * 3 * N;
-    double *acc = acc_all + (int64_t)blockIdx.y * 5 * N;
-    const int kx0 = blockIdx.x * CPW;
-    for (int i = threadIdx.x; i < L * CPW; i += kBlock) {
-        const int y = i / CPW, c = i - y * CPW;
-        const int br = (int)(__brev((unsigned)y) >> (32 - logL));
-#pragma unroll
-        for (int ch = 0; ch < 3; ++ch) buf[(ch * CPW + c) * L + br] = X[ch * N + (int64_t)y * L + kx0 + c];
-    }
-    __syncthreads();
-    k2_fft_lines<3 * CPW>(buf, L, L, twid);
-    for (int i = threadIdx.x; i < L * CPW; i += kBlock) {
-        const int ky = i / CPW, c = i - ky * CPW;
-        double re[3], im[3];
+// PAR: the three channels of the columns side by side (3 cols L <= U NT), the
+// shorter chain, for launches that leave CUs idle; else one after the other,
+// the transformed values waiting in registers (cols L <= U NT): more adjacent
+// columns a workgroup, so each row is read as cols consecutive values.
+template <int NT, int U, bool PAR>
+__global__ void __launch_bounds__(NT)
+k2_spec_cols(int L, FftPlan p, int cols, const double2 *__restrict__ X_all, const double2 *__restrict__ tw,
+             double *__restrict__ acc_all) {
+    __shared__ double2 S[U * NT + U * NT / 8 + 64];
+    __shared__ double2 s_tw[NT <= kTwLds ? kTwLds : 1];
+    const int Lh = L / 2 + 1, stride = fft_stride(L), kx0 = blockIdx.x * cols;
+    const double2 *X = X_all + (int64_t)blockIdx.y * 3 * L * Lh;
+    double *acc = acc_all + (int64_t)blockIdx.y * k2_acc_len(L);
+    const bool in_lds = NT <= kTwLds && L <= kTwLds;
+    if (in_lds)
+        for (int k = threadIdx.x; k < L; k += NT) s_tw[k] = tw[k];
+    const double2 *t = in_lds ? s_tw : tw;
+    const float r_c = 1.0f / (float)cols, r_L = 1.0f / (float)L;
+    auto load = [&](int c0, int nc) {  // channels c0 .. c0 + nc - 1
+        for (int i = threadIdx.x; i < nc * L * cols; i += NT) {
+            const int cy = div_small(i, r_c), c = i - cy * cols, ch = div_small(cy, r_L), y = cy - ch * L;
+            S[(ch * cols + c) * stride + fft_slot(y)] =
+                kx0 + c < Lh ? X[((int64_t)(c0 + ch) * L + y) * Lh + kx0 + c] : make_double2(0.0, 0.0);
+        }
+        __syncthreads();
+    };
+    if constexpr (PAR) {
+        load(0, 3);
+        fft_lines<NT, U>(S, 3 * cols, p, t);
+        for (int i = threadIdx.x; i < cols * L; i += NT) {
+            const int c = div_small(i, r_L), ky = i - c * L, e = fft_slot(ky);
+            if (kx0 + c < Lh)
+                k2_spec_add(acc, L, ky, kx0 + c, S[c * stride + e], S[(cols + c) * stride + e],
+                            S[(2 * cols + c) * stride + e]);
+        }
+    } else {
+        double2 v[3][U];
 #pragma unroll
         for (int ch = 0; ch < 3; ++ch) {
-            const double2 v = buf[(ch * CPW + c) * L + ky];
-            re[ch] = v.x;
-            im[ch] = v.y;
+            load(ch, 1);
+            fft_lines<NT, U>(S, cols, p, t);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = threadIdx.x + u * NT, c = div_small(i, r_L);
+                if (i < cols * L) v[ch][u] = S[c * stride + fft_slot(i - c * L)];
+            }
+            __syncthreads();
         }
-        k2_spec_add(acc, N, L, ky, kx0 + c, re, im);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = threadIdx.x + u * NT, c = div_small(i, r_L), ky = i - c * L;
+            if (i < cols * L && kx0 + c < Lh) k2_spec_add(acc, L, ky, kx0 + c, v[0][u], v[1][u], v[2][u]);
+        }
     }
+}
+
+// The spectra [5][ky][kx] of all modes from the accumulators of one replica:
+// modes with kx > L/2 from their mirror images.  32 x 32 modes a workgroup,
+// transposed through LDS.
+__global__ void __launch_bounds__(kBlock)
+k2_spec_full(int L, const double *__restrict__ acc, double *__restrict__ out) {
+    __shared__ double T[32][33];
+    const int Lh = L / 2 + 1, c = blockIdx.z, a = threadIdx.x & 31, b = threadIdx.x >> 5;
+    const int x0 = blockIdx.x * 32, y0 = blockIdx.y * 32;
+    const int64_t A = (int64_t)Lh * L;
+    for (int k = b; k < 32; k += kBlock / 32) {
+        const int kx = x0 + k, ky = y0 + a;
+        if (kx >= L || ky >= L) continue;
+        int64_t src;
+        if (kx < Lh) src = c * A + (int64_t)kx * L + ky;
+        else if (c >= 3 && 2 * ky == L) src = 5 * A + (c - 3) * Lh + (L - kx);
+        else src = c * A + (int64_t)(L - kx) * L + (ky == 0 ? 0 : L - ky);
+        T[k][a] = acc[src];
+    }
+    __syncthreads();
+    for (int k = b; k < 32; k += kBlock / 32) {
+        const int kx = x0 + a, ky = y0 + k;
+        if (kx < L && ky < L) out[(int64_t)c * L * L + (int64_t)ky * L + kx] = T[a][k];
+    }
+}
+
+// The launches of a sample of R replicas: as many rows or columns a workgroup
+// as its 4 points a thread hold, 256 threads where the lines are short.
+struct K2SpecPlan {
+    FftPlan row, col;
+    int row_nt, rows, col_nt, cols;
+    bool par;
+};
+
+inline K2SpecPlan k2_spec_plan(int L, int R) {
+    K2SpecPlan s{};
+    s.row = L % 2 == 0 ? fft_plan(L / 2, 2) : fft_plan(L, 1);
+    s.col = fft_plan(L, 1);
+    const int n = s.row.n, Lh = L / 2 + 1;
+    s.row_nt = 3 * n <= 1024 ? 256 : (3 * n <= 2048 ? 512 : 1024);
+    s.rows = std::max(1, std::min(4 * s.row_nt / (3 * n), 8));
+    while (s.rows > 1 && (int64_t)R * ((L + s.rows - 1) / s.rows) < 256) --s.rows;
+    // three channels side by side while the columns would not fill the chip
+    s.par = 3 * L <= 4096 && (int64_t)R * Lh <= 1024;
+    s.col_nt = s.par ? (3 * L <= 1024 ? 256 : (3 * L <= 2048 ? 512 : 1024)) : (L <= 256 ? 256 : (L <= 512 ? 512 : 1024));
+    s.cols = s.par ? 1 : std::max(1, std::min(4 * s.col_nt / L, 8));
+    return s;
+}
+
+inline void launch_k2_spectra(const K2SpecPlan &s, int L, int R, const float *pop, const double2 *tw, double2 *X,
+                              double *acc, hipStream_t stream) {
+    const dim3 gr((unsigned)((L + s.rows - 1) / s.rows), (unsigned)R);
+    const dim3 gc((unsigned)((L / 2 + s.cols) / s.cols), (unsigned)R);
+#define LBFSS_ROWS(NT_, U_) \
+    hipLaunchKernelGGL((k2_spec_rows<NT_, U_>), gr, dim3(NT_), 0, stream, L, s.row, s.rows, pop, tw, X)
+#define LBFSS_COLS(NT_, PAR_)                                                                             \
+    hipLaunchKernelGGL((k2_spec_cols<NT_, 4, PAR_>), gc, dim3(NT_), 0, stream, L, s.col, s.cols,          \
+                       (const double2 *)X, tw, acc)
+    if (s.row_nt == 256) LBFSS_ROWS(256, 4);
+    else if (s.row_nt == 512) LBFSS_ROWS(512, 4);
+    else if (3 * s.row.n <= 4096) LBFSS_ROWS(1024, 4);
+    else LBFSS_ROWS(1024, 8);  // odd L from 1367
+    if (s.par) {
+        if (s.col_nt == 256) LBFSS_COLS(256, true);
+        else if (s.col_nt == 512) LBFSS_COLS(512, true);
+        else LBFSS_COLS(1024, true);
+    } else {
+        if (s.col_nt == 256) LBFSS_COLS(256, false);
+        else if (s.col_nt == 512) LBFSS_COLS(512, false);
+        else LBFSS_COLS(1024, false);
+    }
+#undef LBFSS_ROWS
+#undef LBFSS_COLS
 }
 
 }  // namespace lbfss
