@@ -19,6 +19,7 @@
 #include "lbfss_d2q9.hpp"
 #include "lbfss_meq.hpp"
 #include "lbfss_block.hpp"
+#include "lbfss_hostcopy.hpp"
 
 using namespace lbfss;
 
@@ -1264,13 +1265,13 @@ int lb_fields(lb_sim *s, int replica, double *rho, double *j, double *f) {
                                (const float *)s->pop[cur] + Q * d.site_off, drho, dj, df);
         if (hipGetLastError() != hipSuccess) rc = LB_EDEVICE;
     }
-    if (rc == LB_OK && rho && hipMemcpyAsync(rho, drho, sizeof(double) * N, hipMemcpyDeviceToHost, s->stream))
-        rc = LB_EDEVICE;
-    if (rc == LB_OK && j && hipMemcpyAsync(j, dj, sizeof(double) * 3 * N, hipMemcpyDeviceToHost, s->stream))
-        rc = LB_EDEVICE;
-    if (rc == LB_OK && f && hipMemcpyAsync(f, df, sizeof(double) * Q * N, hipMemcpyDeviceToHost, s->stream))
-        rc = LB_EDEVICE;
-    if (hipStreamSynchronize(s->stream) != hipSuccess && rc == LB_OK) rc = LB_EDEVICE;
+    {
+        HostStage stage(s->stream, s->device);
+        if (rc == LB_OK && rho && stage.to_host(rho, drho, sizeof(double) * N)) rc = LB_EDEVICE;
+        if (rc == LB_OK && j && stage.to_host(j, dj, sizeof(double) * 3 * N)) rc = LB_EDEVICE;
+        if (rc == LB_OK && f && stage.to_host(f, df, sizeof(double) * Q * N)) rc = LB_EDEVICE;
+        if (hipStreamSynchronize(s->stream) != hipSuccess && rc == LB_OK) rc = LB_EDEVICE;
+    }
     dev_release(s, df, sizeof(double) * Q * N);
     dev_release(s, dj, sizeof(double) * 3 * N);
     dev_release(s, drho, sizeof(double) * N);
@@ -1320,7 +1321,8 @@ int lb_set_populations(lb_sim *s, int replica, const double *f) {
     if (!df) return LB_ENOMEM;
     int rc = LB_OK;
     const int cur = (int)(s->t & 1);
-    if (hipMemcpyAsync(df, f, bytes, hipMemcpyHostToDevice, s->stream) != hipSuccess) rc = LB_EDEVICE;
+    HostStage stage(s->stream, s->device);
+    if (stage.to_device(df, f, bytes) != hipSuccess) rc = LB_EDEVICE;
     if (rc == LB_OK) {
         const unsigned nb = (unsigned)ceil_div(d.N, kBlock);
         if (s->storage == LB_FP16)
@@ -1591,6 +1593,7 @@ const char *lb_strerror(int code) {
 // The paper's own D2Q9 model (kernels in lbfss_d2q9.hpp).
 // ---------------------------------------------------------------------------
 struct lb2_sim {
+    int device = 0;
     int L = 0;
     int nrep = 0;
     int sample_every = 0;
@@ -1654,6 +1657,7 @@ int lb2_create_batch(int n, int L, const lb2_params *p, const uint64_t *seeds, l
         lb2_destroy(s);
         return code;
     };
+    if (hipGetDevice(&s->device) != hipSuccess) return fail(LB_EDEVICE);
     if (hipStreamCreateWithFlags(&s->own_stream, hipStreamNonBlocking) != hipSuccess) return fail(LB_EDEVICE);
     s->stream = s->own_stream;
     for (int r = 0; r < n; ++r) {
@@ -1764,10 +1768,13 @@ int lb2_fields(lb2_sim *s, int replica, double *rho, double *j, double *f) {
     hipLaunchKernelGGL(k2_export, dim3((unsigned)ceil_div(N, kBlock)), dim3(kBlock), 0, s->stream, s->D[replica],
                        (const float *)s->pop[s->t & 1] + (int64_t)replica * Q2 * N, dr, dj, df);
     if (hipGetLastError() != hipSuccess) rc = LB_EDEVICE;
-    if (rc == LB_OK && rho && hipMemcpyAsync(rho, dr, sizeof(double) * N, hipMemcpyDeviceToHost, s->stream)) rc = LB_EDEVICE;
-    if (rc == LB_OK && j && hipMemcpyAsync(j, dj, sizeof(double) * 2 * N, hipMemcpyDeviceToHost, s->stream)) rc = LB_EDEVICE;
-    if (rc == LB_OK && f && hipMemcpyAsync(f, df, sizeof(double) * Q2 * N, hipMemcpyDeviceToHost, s->stream)) rc = LB_EDEVICE;
-    if (hipStreamSynchronize(s->stream) != hipSuccess && rc == LB_OK) rc = LB_EDEVICE;
+    {
+        HostStage stage(s->stream, s->device);
+        if (rc == LB_OK && rho && stage.to_host(rho, dr, sizeof(double) * N)) rc = LB_EDEVICE;
+        if (rc == LB_OK && j && stage.to_host(j, dj, sizeof(double) * 2 * N)) rc = LB_EDEVICE;
+        if (rc == LB_OK && f && stage.to_host(f, df, sizeof(double) * Q2 * N)) rc = LB_EDEVICE;
+        if (hipStreamSynchronize(s->stream) != hipSuccess && rc == LB_OK) rc = LB_EDEVICE;
+    }
     s->blocks.pop_back();
     if (s->alloc.free_) s->alloc.free_(buf, s->alloc.ctx);
     else (void)hipFree(buf);
@@ -1780,7 +1787,8 @@ int lb2_set_populations(lb2_sim *s, int replica, const double *f) {
     double *df = (double *)dev_alloc2(s, sizeof(double) * Q2 * N);
     if (!df) return LB_ENOMEM;
     int rc = LB_OK;
-    if (hipMemcpyAsync(df, f, sizeof(double) * Q2 * N, hipMemcpyHostToDevice, s->stream) != hipSuccess) rc = LB_EDEVICE;
+    HostStage stage(s->stream, s->device);
+    if (stage.to_device(df, f, sizeof(double) * Q2 * N) != hipSuccess) rc = LB_EDEVICE;
     if (rc == LB_OK) {
         hipLaunchKernelGGL(k2_import, dim3((unsigned)ceil_div(N, kBlock)), dim3(kBlock), 0, s->stream, s->D[replica],
                            (const double *)df, s->pop[s->t & 1] + (int64_t)replica * Q2 * N);
@@ -1805,10 +1813,9 @@ int lb2_spectra(lb2_sim *s, int replica, int64_t *n_samples, double *S, double *
                        (const double *)s->d_acc + (int64_t)replica * k2_acc_len(L), acc);
     if (hipGetLastError() != hipSuccess) return LB_EDEVICE;
     double *dst[5] = {S, Jx, Jy, Jpar, Jperp};
+    HostStage stage(s->stream, s->device);
     for (int c = 0; c < 5; ++c)
-        if (dst[c] && hipMemcpyAsync(dst[c], acc + c * N, sizeof(double) * N, hipMemcpyDeviceToHost, s->stream) !=
-                          hipSuccess)
-            return LB_EDEVICE;
+        if (dst[c] && stage.to_host(dst[c], acc + c * N, sizeof(double) * N) != hipSuccess) return LB_EDEVICE;
     if (hipStreamSynchronize(s->stream) != hipSuccess) return LB_EDEVICE;
     *n_samples = s->n_samples;
     return check2(s);
