@@ -1604,6 +1604,7 @@ struct lb2_sim {
     Allocator alloc;
     std::vector<void *> blocks;
     float *pop[2] = {nullptr, nullptr};  // [replica][9][L^2]
+    int cur = 0;                         // the buffer that holds the state
     float *d_drho = nullptr;
     int *d_err = nullptr;
     double2 *d_twid = nullptr;  // e^{-2 pi i k / L}
@@ -1724,18 +1725,43 @@ int check2(lb2_sim *s) {
 }
 }  // namespace
 
+// Steps of one launch: several for small lattices, at most up to the next
+// sample.  Up to two tiles a CU three steps (256^2: 2.39 us a step, two 2.70,
+// one 4.0-4.2, four 2.41; 320^2: 3.4, 3.6, 4.6, 3.6), up to four tiles two
+// (512^2: 5.6 in twos, 6.0 in threes, 6.2 alone; 32 x 128^2, eight tiles a
+// CU: 9.4 in twos, 9.2 alone).  A rest of four is taken as two twos.
+static int k2_steps_per_launch(const lb2_sim *s, int64_t left) {
+    const int64_t tiles = ceil_div(s->L, K2F_T) * ceil_div(s->L, K2F_T) * s->nrep;
+    if (tiles > 1024 || left == 1) return 1;
+    return tiles > 512 || left == 2 || left == 4 ? 2 : 3;
+}
+
 int lb2_step(lb2_sim *s, int64_t n) {
     if (!s || n < 0) return LB_EINVAL;
     const int tiles = (int)(ceil_div(s->L, K2TX) * ceil_div(s->L, K2TY));
+    const int ftiles = (int)(ceil_div(s->L, K2F_T) * ceil_div(s->L, K2F_T));
     const unsigned R = (unsigned)s->nrep;
-    for (int64_t k = 0; k < n; ++k) {
-        const int cur = (int)(s->t & 1);
-        hipLaunchKernelGGL(s->nrep > 1 ? k2_step_tiled<true> : k2_step_tiled<false>, dim3((unsigned)tiles * R),
-                           dim3(K2TX * K2TY), 0, s->stream, s->D[0], (const D2Desc *)s->d_desc, tiles,
-                           (const float *)s->pop[cur], s->pop[cur ^ 1], (uint64_t)s->t, s->d_err);
-        s->t += 1;
-        if (s->sample_every > 0 && s->t % s->sample_every == 0) {
-            launch_k2_spectra(s->spec, s->L, s->nrep, s->pop[cur ^ 1], s->d_twid, s->d_X, s->d_acc, s->stream);
+    while (n > 0) {
+        const int64_t e = s->sample_every;
+        const int64_t left = e > 0 ? std::min<int64_t>(n, e - s->t % e) : n;
+        const float *in = s->pop[s->cur];
+        float *out = s->pop[s->cur ^ 1];
+        const int K = k2_steps_per_launch(s, left);
+        if (K == 1)
+            hipLaunchKernelGGL(s->nrep > 1 ? k2_step_tiled<true> : k2_step_tiled<false>, dim3((unsigned)tiles * R),
+                               dim3(K2TX * K2TY), 0, s->stream, s->D[0], (const D2Desc *)s->d_desc, tiles, in, out,
+                               (uint64_t)s->t, s->d_err);
+        else if (K == 2)
+            hipLaunchKernelGGL(k2_steps_fused<2>, dim3((unsigned)ftiles * R), dim3(K2Fused<2>::NT), 0, s->stream,
+                               (const D2Desc *)s->d_desc, ftiles, in, out, (uint64_t)s->t, s->d_err);
+        else
+            hipLaunchKernelGGL(k2_steps_fused<3>, dim3((unsigned)ftiles * R), dim3(K2Fused<3>::NT), 0, s->stream,
+                               (const D2Desc *)s->d_desc, ftiles, in, out, (uint64_t)s->t, s->d_err);
+        s->cur ^= 1;
+        s->t += K;
+        n -= K;
+        if (e > 0 && s->t % e == 0) {
+            launch_k2_spectra(s->spec, s->L, s->nrep, s->pop[s->cur], s->d_twid, s->d_X, s->d_acc, s->stream);
             s->n_samples += 1;
         }
     }
@@ -1766,7 +1792,7 @@ int lb2_fields(lb2_sim *s, int replica, double *rho, double *j, double *f) {
     double *df = f ? buf + (rho ? N : 0) + (j ? 2 * N : 0) : nullptr;
     int rc = LB_OK;
     hipLaunchKernelGGL(k2_export, dim3((unsigned)ceil_div(N, kBlock)), dim3(kBlock), 0, s->stream, s->D[replica],
-                       (const float *)s->pop[s->t & 1] + (int64_t)replica * Q2 * N, dr, dj, df);
+                       (const float *)s->pop[s->cur] + (int64_t)replica * Q2 * N, dr, dj, df);
     if (hipGetLastError() != hipSuccess) rc = LB_EDEVICE;
     {
         HostStage stage(s->stream, s->device);
@@ -1791,7 +1817,7 @@ int lb2_set_populations(lb2_sim *s, int replica, const double *f) {
     if (stage.to_device(df, f, sizeof(double) * Q2 * N) != hipSuccess) rc = LB_EDEVICE;
     if (rc == LB_OK) {
         hipLaunchKernelGGL(k2_import, dim3((unsigned)ceil_div(N, kBlock)), dim3(kBlock), 0, s->stream, s->D[replica],
-                           (const double *)df, s->pop[s->t & 1] + (int64_t)replica * Q2 * N);
+                           (const double *)df, s->pop[s->cur] + (int64_t)replica * Q2 * N);
         if (hipGetLastError() != hipSuccess) rc = LB_EDEVICE;
     }
     if (hipStreamSynchronize(s->stream) != hipSuccess && rc == LB_OK) rc = LB_EDEVICE;

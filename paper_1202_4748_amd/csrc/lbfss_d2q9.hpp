@@ -90,14 +90,28 @@ __host__ __device__ constexpr bool k2_pairs_ok() {
 }
 static_assert(k2_pairs_ok(), "opposite velocity pairs and basis parities");
 
+// The six collision normals of (site, step): Philox calls 0 and 1.
+struct K2Normals {
+    float g[6];
+};
+__device__ __forceinline__ K2Normals k2_normals(const D2Desc &D, uint32_t s, uint64_t t) {
+    const Words4 w0 = philox4x32_10(s, (uint32_t)t, 0u, (uint32_t)(t >> 32), D.key0, D.key1);
+    const Words4 w1 = philox4x32_10(s, (uint32_t)t, 1u, (uint32_t)(t >> 32), D.key0, D.key1);
+    const float r0 = bm_radius(uniform01(w0.v[0])), a0 = uniform01(w0.v[1]);
+    const float r1 = bm_radius(uniform01(w0.v[2])), a1 = uniform01(w0.v[3]);
+    const float r2 = bm_radius(uniform01(w1.v[0])), a2 = uniform01(w1.v[1]);
+    return K2Normals{{r0 * cos_rev(a0), r0 * sin_rev(a0), r1 * cos_rev(a1), r1 * sin_rev(a1), r2 * cos_rev(a2),
+                      r2 * sin_rev(a2)}};
+}
+
 // The collision of one site: d holds its nine pulled deviations and
 // receives the post-collision ones (stored unshifted: the next step pulls);
 // at(dx, dy) is the density deviation of a neighbour (the same sum drho2 of
-// its pulled values); s is the site index, t the step (the noise counter).
+// its pulled values); normals() gives its collision normals.
 // Moments, equilibrium, relaxation, noise, back-transform.  Returns false
 // where rho or the noise covariance leaves its domain.
-template <typename F>
-__device__ __forceinline__ bool k2_collide_site(const D2Desc &D, float (&d)[Q2], F &&at, uint32_t s, uint64_t t) {
+template <typename F, typename G>
+__device__ __forceinline__ bool k2_collide_site(const D2Desc &D, float (&d)[Q2], F &&at, G &&normals) {
     // moment deviations, from the rest value and the pair sums (even
     // moments) or differences (odd moments)
     float ps[4], pd[4];
@@ -160,14 +174,8 @@ __device__ __forceinline__ bool k2_collide_site(const D2Desc &D, float (&d)[Q2],
         bad |= !(A > 0.0f) || !(R > 0.0f);
         const float L88 = __builtin_amdgcn_sqrtf(R);
         const float sig = D.noise_amp * __builtin_amdgcn_sqrtf(rho);
-        const Words4 w0 = philox4x32_10(s, (uint32_t)t, 0u, (uint32_t)(t >> 32), D.key0, D.key1);
-        const Words4 w1 = philox4x32_10(s, (uint32_t)t, 1u, (uint32_t)(t >> 32), D.key0, D.key1);
-        const float r0 = bm_radius(uniform01(w0.v[0])), a0 = uniform01(w0.v[1]);
-        const float r1 = bm_radius(uniform01(w0.v[2])), a1 = uniform01(w0.v[3]);
-        const float r2 = bm_radius(uniform01(w1.v[0])), a2 = uniform01(w1.v[1]);
-        const float g0 = r0 * cos_rev(a0), g1 = r0 * sin_rev(a0);
-        const float g2n = r1 * cos_rev(a1), g3 = r1 * sin_rev(a1);
-        const float g4 = r2 * cos_rev(a2), g5 = r2 * sin_rev(a2);
+        const K2Normals n = normals();
+        const float g0 = n.g[0], g1 = n.g[1], g2n = n.g[2], g3 = n.g[3], g4 = n.g[4], g5 = n.g[5];
         m[3] += sig * L33 * g0;
         m[4] += sig * (2.0f / 3.0f) * g1;
         m[5] += sig * (1.0f / 3.0f) * g2n;
@@ -263,9 +271,93 @@ k2_step_tiled(D2Desc D0, const D2Desc *__restrict__ descs, int tiles_per_rep, co
     __syncthreads();
     if (!inner) return;
     const uint32_t s = (uint32_t)(x0 + ix) + (uint32_t)L * (uint32_t)(y0 + iy);
-    const bool ok = k2_collide_site(D, d, [&](int dx, int dy) { return s_rho[r_in + dy * EX + dx]; }, s, t);
+    const bool ok = k2_collide_site(
+        D, d, [&](int dx, int dy) { return s_rho[r_in + dy * EX + dx]; }, [&] { return k2_normals(D, s, t); });
 #pragma unroll
     for (int i = 0; i < Q2; ++i) pop_out[i * N + s] = d[i];
+    if (!ok) *err = 1;
+}
+
+// K steps in one launch, for lattices that leave most of the chip idle: a
+// step on its own is then one chain of launch, loads and collision, 4.0 us at
+// 256^2 (256 workgroups, one wave per SIMD) of which the arithmetic is a
+// quarter.  A workgroup owns a 16 x 16 tile; step k collides the tile with a
+// rim of 2 (K - 1 - k) sites around it, whose neighbours' post-collision
+// populations of the step before lie in LDS (a step needs the pulls, one site
+// away, of the sites it collides and of their neighbours, for the density).
+// The first step pulls from memory, the last stores the tile.  Rims are
+// computed by every workgroup that needs them, from the same values in the
+// same order, so the result does not depend on K.  Positions wrap, so a tile
+// may stick out of the lattice or be wider than it.  The rims cost 1.6 times
+// the collisions at K = 3; what is left at 256^2 is the chain of three
+// collisions, about 1.5 us each, and one launch: 4.0 -> 2.39 us a step.
+constexpr int K2F_T = 16;
+template <int K>
+struct K2Fused {
+    static constexpr int C0 = K2F_T + 4 * (K - 1);  // edge of the first step's collided square
+    static constexpr int E0 = C0 + 2;               // edge of its density square
+    static constexpr int NT = (E0 * E0 + 63) / 64 * 64;
+};
+
+// v in [-2 K, L + 16 + 2 K) to [0, L); rL = 1 / L to an ulp
+__device__ __forceinline__ int k2_wrap(int v, int L, float rL) {
+    return v - L * (int)floorf(((float)v + 0.5f) * rL);
+}
+
+template <int K>
+__global__ void __launch_bounds__(K2Fused<K>::NT)
+k2_steps_fused(const D2Desc *__restrict__ descs, int tiles_per_rep, const float *__restrict__ pop_all,
+               float *__restrict__ pop_out_all, uint64_t t, int *__restrict__ err) {
+    constexpr int C0 = K2Fused<K>::C0, E0 = K2Fused<K>::E0;
+    __shared__ float s_pop[Q2][C0 * C0];
+    __shared__ float s_rho[E0 * E0];
+    const int gtile = xcd_tile(blockIdx.x, gridDim.x);
+    const int rep = gtile / tiles_per_rep, tile = gtile - rep * tiles_per_rep;
+    const D2Desc D = descs[rep];
+    const int L = D.L, ntx = (L + K2F_T - 1) / K2F_T, x0 = (tile % ntx) * K2F_T, y0 = (tile / ntx) * K2F_T;
+    const int64_t N = (int64_t)L * L;
+    const float *pop = pop_all + (int64_t)rep * Q2 * N;
+    float *pop_out = pop_out_all + (int64_t)rep * Q2 * N;
+    const float rL = __builtin_amdgcn_rcpf((float)L);
+    const int tid = threadIdx.x;
+    bool ok = true;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        // this thread's site of the step's density square (edge E), one site
+        // wider on each side than the square collided (edge C)
+        const int C = K2F_T + 4 * (K - 1 - k), E = C + 2, rim = 2 * (K - 1 - k) + 1;
+        const int ey = tid / E, ex = tid - ey * E;
+        const bool on = ey < E, in = on && ex >= 1 && ex <= C && ey >= 1 && ey <= C;
+        const int x = k2_wrap(x0 - rim + ex, L, rL), y = k2_wrap(y0 - rim + ey, L, rL);
+        const uint32_t site = (uint32_t)(x + L * y);
+        float d[Q2];
+        K2Normals n;
+        if (k == 0) {
+            if (on) pull2(pop, L, x, y, d);
+            n = k2_normals(D, site, t);  // while the pulls are on their way
+        } else if (on) {
+            const int c = (ey + 1) * (C + 4) + ex + 1;  // the site in the square the step before collided
+#pragma unroll
+            for (int i = 0; i < Q2; ++i) d[i] = s_pop[i][c - c2y(i) * (C + 4) - c2x(i)];
+        }
+        if (on) s_rho[tid] = drho2(d);
+        __syncthreads();
+        if (in) {
+            const float *r = s_rho + tid;
+            ok &= k2_collide_site(
+                D, d, [&](int dx, int dy) { return r[dy * E + dx]; },
+                [&] { return k == 0 ? n : k2_normals(D, site, t + (uint64_t)k); });
+            if (k + 1 < K) {
+                const int c = (ey - 1) * C + ex - 1;
+#pragma unroll
+                for (int i = 0; i < Q2; ++i) s_pop[i][c] = d[i];
+            } else if (x0 + ex - 1 < L && y0 + ey - 1 < L) {
+#pragma unroll
+                for (int i = 0; i < Q2; ++i) pop_out[i * N + site] = d[i];
+            }
+        }
+        if (k + 1 < K) __syncthreads();
+    }
     if (!ok) *err = 1;
 }
 
