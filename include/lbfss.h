@@ -167,8 +167,7 @@ enum {
                            * (FP32 storage; FP16 handles run FUSED) */
     LB_KERNEL_ROWS = 3    /* as STAGED, the staging copies the source rows of each population
                            * with 16-byte loads (FP32 or FP16 storage); every L a multiple
-                           * of 4 (FP32) or 8 (FP16), else LB_EINVAL.  FP32 plans on 64 x 8
-                           * tiles run their sample steps on 64 x 4 tiles (same results) */
+                           * of 4 (FP32) or 8 (FP16), else LB_EINVAL */
 };
 
 typedef struct {

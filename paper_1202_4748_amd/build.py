@@ -192,11 +192,11 @@ def check_counted_wait_order(asm: str):
 
 
 # staged instances the host launches on large lattices and the waves per
-# SIMD each must keep: two 512-thread workgroups per CU on 64 x 8 tiles (the
-# FP32 snapshot instance is not launched there: sample steps of those plans
-# run on 64 x 4 tiles), three 256-thread ones on 64 x 4
+# SIMD each must keep: two 512-thread workgroups per CU on 64 x 8 tiles, three
+# 256-thread ones on 64 x 4
 REQUIRED_OCCUPANCY = {
     "_ZN5lbfss14k_fused_stagedIfLi64ELi8ELb1ELb0E": 4,
+    "_ZN5lbfss14k_fused_stagedIfLi64ELi8ELb1ELb1E": 4,
     "_ZN5lbfss14k_fused_stagedI6__halfLi64ELi8ELb1ELb0E": 4,
     "_ZN5lbfss14k_fused_stagedI6__halfLi64ELi8ELb1ELb1E": 4,
     "_ZN5lbfss14k_fused_stagedIfLi64ELi4ELb1ELb0E": 3,

@@ -138,11 +138,6 @@ struct lb_sim {
     FusedTile *d_tiles = nullptr;
     int n_tiles = 0;
     int tiles_for[3] = {0, 0, 0};
-    // sample steps of FP32 rows plans on 512-thread tiles run the snapshot
-    // kernel on tiles of its own (see rows_snap_tile)
-    FusedTile *d_tiles_snap = nullptr;
-    int n_tiles_snap = 0;
-    int snap_tiles_for[3] = {0, 0, 0};
 
     int64_t t = 0;
     lb_plan plan{LB_KERNEL_SPLIT, 0, 0, 0, 0, 0};
@@ -291,12 +286,8 @@ void launch_step(lb_sim *s, int cur, int koff, float *snap) {
         return;
     }
     if (s->plan.kernel == LB_KERNEL_ROWS && s->n_tiles > 0) {
-        if (snap && s->n_tiles_snap > 0)
-            launch_fused_staged<T, true>(s->d_desc, s->d_tiles_snap, s->n_tiles_snap, in, out, s->d_step, koff,
-                                         s->d_err, s->snap_tiles_for[0], s->snap_tiles_for[1], s->stream, snap, total);
-        else
-            launch_fused_staged<T, true>(s->d_desc, s->d_tiles, s->n_tiles, in, out, s->d_step, koff, s->d_err,
-                                         s->plan.tile_x, s->plan.tile_y, s->stream, snap, total);
+        launch_fused_staged<T, true>(s->d_desc, s->d_tiles, s->n_tiles, in, out, s->d_step, koff, s->d_err,
+                                     s->plan.tile_x, s->plan.tile_y, s->stream, snap, total);
         return;
     }
     if (s->plan.kernel == LB_KERNEL_STAGED && s->n_tiles > 0 && std::is_same<T, float>::value) {
@@ -740,35 +731,6 @@ int build_tiles(lb_sim *s, int tx, int ty, int tz) {
     return LB_OK;
 }
 
-// The snapshot tile table of a plan: built where rows_snap_tile asks for one,
-// released otherwise (after the stream and any graph that reads it are done).
-int build_snap_tiles(lb_sim *s, const lb_plan &p) {
-    int tx = 0, ty = 0, tz = 0;
-    const bool want = p.kernel == LB_KERNEL_ROWS && !s->eq_pressure &&
-                      rows_snap_tile(s->hdesc, s->storage == LB_FP32, p.tile_x, p.tile_y, p.tile_z, tx, ty, tz);
-    if (want && s->d_tiles_snap && s->snap_tiles_for[0] == tx && s->snap_tiles_for[1] == ty &&
-        s->snap_tiles_for[2] == tz)
-        return LB_OK;
-    if (s->d_tiles_snap) {
-        HIPCHK(hipStreamSynchronize(s->stream));
-        drop_graph(s);
-        dev_release(s, s->d_tiles_snap, sizeof(FusedTile) * std::max<size_t>((size_t)s->n_tiles_snap, 1));
-        s->d_tiles_snap = nullptr;
-        s->n_tiles_snap = 0;
-        s->snap_tiles_for[0] = s->snap_tiles_for[1] = s->snap_tiles_for[2] = 0;
-    }
-    if (!want) return LB_OK;
-    std::vector<FusedTile> tiles;
-    if (make_fused_tiles(s->hdesc, tx, ty, tz, tiles) != 0) return LB_EINVAL;
-    int rc = upload(s, &s->d_tiles_snap, tiles);
-    if (rc) return rc;
-    s->n_tiles_snap = (int)tiles.size();
-    s->snap_tiles_for[0] = tx;
-    s->snap_tiles_for[1] = ty;
-    s->snap_tiles_for[2] = tz;
-    return LB_OK;
-}
-
 // Blocks (or tiles) of a shape over all replicas, and the sites they span.
 void count_tiles(const lb_sim *s, int tx, int ty, int tz, int64_t *n, int64_t *span) {
     *n = *span = 0;
@@ -1006,19 +968,22 @@ int lb_sync(lb_sim *s) {
 
 int lb_moments(lb_sim *s, int replica, lb_moments_t *out, double *sk, double *series) {
     if (!s || !out || replica < 0 || replica >= s->nrep) return LB_EINVAL;
+    const bool summed = s->pending;  // the sample due on this state, taken now, forms the same row and plane sums
     flush_pending(s);
     const SampDesc &d = s->hsd[replica];
     const RepDesc &rd = s->hdesc[replica];
-    const int cur = (int)(s->t & 1);
-    const unsigned nrows = (unsigned)ceil_div((int64_t)d.L * d.L, kBlock / 64);
-    if (s->storage == LB_FP16)
-        hipLaunchKernelGGL(k_state_rows<__half>, dim3(nrows), dim3(kBlock), 0, s->stream, rd,
-                           (const __half *)s->pop[cur] + Q * rd.site_off, s->d_ws + d.rows_off);
-    else
-        hipLaunchKernelGGL(k_state_rows<float>, dim3(nrows), dim3(kBlock), 0, s->stream, rd,
-                           (const float *)s->pop[cur] + Q * rd.site_off, s->d_ws + d.rows_off);
-    hipLaunchKernelGGL(k_state_planes, dim3((unsigned)ceil_div(4 * d.L, kBlock / 64)), dim3(kBlock), 0, s->stream,
-                       s->d_sd, replica, s->d_ws);
+    if (!summed) {
+        const int cur = (int)(s->t & 1);
+        const unsigned nrows = (unsigned)ceil_div((int64_t)d.L * d.L, kBlock / 64);
+        if (s->storage == LB_FP16)
+            hipLaunchKernelGGL(k_state_rows<__half>, dim3(nrows), dim3(kBlock), 0, s->stream, rd,
+                               (const __half *)s->pop[cur] + Q * rd.site_off, s->d_ws + d.rows_off);
+        else
+            hipLaunchKernelGGL(k_state_rows<float>, dim3(nrows), dim3(kBlock), 0, s->stream, rd,
+                               (const float *)s->pop[cur] + Q * rd.site_off, s->d_ws + d.rows_off);
+        hipLaunchKernelGGL(k_state_planes, dim3((unsigned)ceil_div(4 * d.L, kBlock / 64)), dim3(kBlock), 0, s->stream,
+                           s->d_sd, replica, s->d_ws);
+    }
     hipLaunchKernelGGL(k_state_report, dim3(1), dim3(kBlock), 0, s->stream, s->d_sd, s->d_desc, replica, s->d_ws,
                        (const double *)s->d_acc, (const int64_t *)s->d_nsamp, (const int *)s->d_err, s->d_report);
     HIPCHK(hipGetLastError());
@@ -1396,7 +1361,6 @@ int lb_set_plan(lb_sim *s, const lb_plan *plan) {
     } else if (!s->eq_pressure) {  // the collide pass has tiles of its own
         if (int rc = build_tiles(s, kSplitTX, kSplitTY, kSplitTZ)) return rc;
     }
-    if (int rc = build_snap_tiles(s, p)) return rc;
     if (p.kernel != s->plan.kernel || p.tile_x != s->plan.tile_x || p.tile_y != s->plan.tile_y ||
         p.tile_z != s->plan.tile_z || p.graph_steps != s->plan.graph_steps)
         drop_graph(s);

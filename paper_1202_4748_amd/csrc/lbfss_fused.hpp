@@ -73,6 +73,11 @@ __device__ __forceinline__ float ldb(const T *p, uint32_t boff) {
 // their halo (the next step reads these values, long after L2 turned over).
 template <typename T>
 __device__ __forceinline__ void stb(T *p, uint32_t boff, float v) {
+    // keeps the offset in its 32-bit register: the compiler would widen it once
+    // and add it to each population's base, 19 64-bit adds a site (256^3 FP32
+    // 606 -> 599 us a step, 512^3 FP16 3.49 -> 3.43 ms; and two registers less,
+    // which lets the 64 x 8 FP32 snapshot instance keep two workgroups per CU)
+    asm("" : "+v"(boff));
     if constexpr (sizeof(T) == 4)
         __builtin_nontemporal_store(v, (float *)((char *)p + boff));
     else
@@ -365,9 +370,12 @@ __device__ __forceinline__ uint32_t pull_off(int q, const PlaneOffs &o) {
 // rectangle entry at the site's row and at column ex + CH - 2 - cx_q.  The
 // rows mode issues about a quarter of the load instructions for the same
 // data.  Tiles of 512 threads (64 x 8) have eight waves; the rest four.
-// 512-thread tiles fit two workgroups per CU (LDS and at most 128 VGPRs)
-// in every instance the host launches; the build checks the VGPR count (a
-// launch-bounds hint to the same effect made the compiler's code slower)
+// 512-thread tiles fit two workgroups per CU (LDS and at most 128 VGPRs); the
+// build checks the VGPR count (a launch-bounds hint to the same effect made
+// the compiler's code slower).  The snapshot instance too: running the sample
+// steps on 64 x 4 tiles instead, as when it was two registers larger, takes
+// 625 against 620 us a step at 256^3 FP32 with a sample every ten, 5115 against
+// 4906 at 512^3.
 //
 // DRAIN: wait for the staged copies and the stores at every barrier, as
 // __syncthreads() would.  Where all tiles of the lattice are resident at once
@@ -774,23 +782,6 @@ inline bool staged_tile_ok(int tx, int ty) {
 inline bool rows_tile_ok(int tx, int ty) {
     return staged_tile_ok(tx, ty) || (tx == 64 && ty == 4) || (tx == 64 && ty == 8);
 }
-
-// With FP32 storage the snapshot instance of the 512-thread rows kernel needs
-// more than the 128 VGPRs of two workgroups per CU, so the sample steps of
-// such a plan run on 64 x 4 tiles (three workgroups per CU; every tile shape
-// gives the same bits), in three z slabs on large lattices.  Returns whether
-// the plan (tx, ty, tz) takes such a table, and its shape.
-inline bool rows_snap_tile(const std::vector<RepDesc> &reps, bool fp32, int tx, int ty, int tz, int &sx, int &sy,
-                           int &sz) {
-    if (!fp32 || tx * ty != 512) return false;
-    int maxL = 0;
-    for (const auto &d : reps) maxL = std::max(maxL, d.L);
-    sx = 64;
-    sy = 4;
-    sz = maxL >= 128 ? (maxL + 2) / 3 : tz;
-    return true;
-}
-
 
 // 64 x 8 tiles resident at once: two workgroups on each of 256 CUs
 constexpr int kOneRound = 512;
