@@ -39,13 +39,19 @@ __device__ __forceinline__ int wrap_far(int v, int L, float rL) {
 
 // The 19 pulled values of site (x, y, z): every load is a scalar base (the
 // population's) plus a 32-bit byte offset (L <= 1024: 4 GiB a population).
-template <typename T>
+// MUL24: the row and plane offsets by the full-rate multiply (factors below
+// 2^24, products modulo 2^32).  A site of the FP32 force model's blocks pulls
+// up to six times and waits on these chains (16^3: 7.53 -> 7.25 us a step,
+// 32^3 8.06 -> 7.72, 64^3 15.6 -> 15.4); the other forms schedule worse with
+// it (FP16 64^3 13.5 -> 14.0, equilibrium model 13.2 -> 13.7).
+template <bool MUL24, typename T>
 __device__ __forceinline__ void pull_site(const T *base, uint32_t N, int L, int x, int y, int z, float (&r)[Q]) {
     constexpr uint32_t S = sizeof(T);
     const uint32_t row = (uint32_t)L * S, plane = (uint32_t)L * row;
     const uint32_t x0 = x * S, xm = wrap_dec(x, L) * S, xp = wrap_inc(x, L) * S;
-    const uint32_t y0 = y * row, ym = wrap_dec(y, L) * row, yp = wrap_inc(y, L) * row;
-    const uint32_t z0 = z * plane, zm = wrap_dec(z, L) * plane, zp = wrap_inc(z, L) * plane;
+    auto mul = [](uint32_t v, uint32_t w) -> uint32_t { return MUL24 ? (uint32_t)__umul24(v, w) : v * w; };
+    const uint32_t y0 = mul(y, row), ym = mul(wrap_dec(y, L), row), yp = mul(wrap_inc(y, L), row);
+    const uint32_t z0 = mul(z, plane), zm = mul(wrap_dec(z, L), plane), zp = mul(wrap_inc(z, L), plane);
 #pragma unroll
     for (int q = 0; q < Q; ++q) {  // source x - c_q
         const int cx = cx_of(q), cy = cy_of(q), cz = cz_of(q);
@@ -64,6 +70,7 @@ k_block(const RepDesc *__restrict__ desc, const FusedTile *__restrict__ tiles, c
     constexpr int NS = TX * TY * TZ;
     static_assert(NS <= NT, "one site per thread");
     constexpr int H = EQ ? 1 : 2;
+    constexpr bool kMul24 = sizeof(T) == 4 && !EQ && !DENS;
     constexpr int EX = TX + 2 * H, EY = TY + 2 * H, EZ = TZ + 2 * H, EP = EX * EY, NE = EP * EZ;
     constexpr int MX = TX + 2, MY = TY + 2, MZ = TZ + 2, MP = MX * MY;
     constexpr int RING = EP - TX * TY;          // halo positions of a plane of the block
@@ -120,7 +127,7 @@ k_block(const RepDesc *__restrict__ desc, const FusedTile *__restrict__ tiles, c
     int x, y, z;
     const uint32_t s = site_of(own ? tid : 0, x, y, z);
     float f[Q];
-    if (own) pull_site(base, N, L, x, y, z, f);
+    if (own) pull_site<kMul24>(base, N, L, x, y, z, f);
     // the threads past the last position load it again
     float hv[KH][DENS ? 1 : Q];
     int hs[KH];
@@ -139,7 +146,7 @@ k_block(const RepDesc *__restrict__ desc, const FusedTile *__restrict__ tiles, c
         const int hx = wrap_far(tl.x0 - H + ex, L, rL), hy = wrap_far(tl.y0 - H + ey, L, rL),
                   hz = wrap_far(tl.z0 - H + ez, L, rL);
         if constexpr (DENS) hv[k][0] = drho[d.site_off + (uint32_t)(hx + L * (hy + L * hz))];
-        else pull_site(base, N, L, hx, hy, hz, hv[k]);
+        else pull_site<kMul24>(base, N, L, hx, hy, hz, hv[k]);
     }
     // the normals, while the loads are on their way
     float gn[16];

@@ -60,13 +60,31 @@ __device__ __forceinline__ int wrap2(int v, int L) { return v < 0 ? v + L : (v >
 // Pulled deviations of site (x, y): d_i(r - c_i).  The three source columns
 // x - c_x and the three source rows y - c_y are wrapped once; each pull is
 // then a 32-bit in-plane offset from the population's (uniform) base.
+// MUL24: the rows' offsets by the full-rate 24-bit multiply (L <= 2048), which
+// the one-step kernel's halo gains from (1000^2 16.4 -> 16.05 us a step, 400 x
+// 100^2 81.9 -> 80.9; 700^2 9.13 -> 9.20) and
+// the kernels of several steps do not (512^2 5.62 -> 5.75).
+template <bool MUL24 = false>
 __device__ __forceinline__ void pull2(const float *__restrict__ pop, int L, int x, int y, float (&d)[Q2]) {
     const uint32_t N = (uint32_t)L * (uint32_t)L;
     const uint32_t col[3] = {(uint32_t)wrap2(x + 1, L), (uint32_t)x, (uint32_t)wrap2(x - 1, L)};  // c_x = -1, 0, 1
-    const uint32_t row[3] = {(uint32_t)wrap2(y + 1, L) * (uint32_t)L, (uint32_t)y * (uint32_t)L,
-                             (uint32_t)wrap2(y - 1, L) * (uint32_t)L};  // c_y = -1, 0, 1
+    auto mul = [](int v, int w) { return MUL24 ? (uint32_t)__umul24(v, w) : (uint32_t)v * (uint32_t)w; };
+    const uint32_t row[3] = {mul(wrap2(y + 1, L), L), mul(y, L), mul(wrap2(y - 1, L), L)};  // c_y = -1, 0, 1
 #pragma unroll
     for (int i = 0; i < Q2; ++i) d[i] = pop[(size_t)i * N + (col[c2x(i) + 1] + row[c2y(i) + 1])];
+}
+
+// The same pulls where y is wave-uniform: the three source rows are scalar
+// bases and a lane adds one of three 32-bit column offsets, no 64-bit or
+// quarter-rate integer arithmetic per lane.
+__device__ __forceinline__ void pull2_row(const float *__restrict__ pop, int L, int x, int y, float (&d)[Q2]) {
+    const uint32_t N = (uint32_t)L * (uint32_t)L;
+    uint32_t col[3] = {4u * (uint32_t)wrap2(x + 1, L), 4u * (uint32_t)x, 4u * (uint32_t)wrap2(x - 1, L)};
+    const uint32_t row[3] = {(uint32_t)wrap2(y + 1, L) * (uint32_t)L, (uint32_t)y * (uint32_t)L,
+                             (uint32_t)wrap2(y - 1, L) * (uint32_t)L};
+    asm("" : "+v"(col[0]), "+v"(col[1]), "+v"(col[2]));  // keeps the offsets in 32-bit registers
+#pragma unroll
+    for (int i = 0; i < Q2; ++i) d[i] = ldb(pop + (size_t)i * N + row[c2y(i) + 1], col[c2x(i) + 1]);
 }
 
 __device__ __forceinline__ float drho2(const float (&d)[Q2]) {
@@ -224,8 +242,21 @@ __device__ __forceinline__ bool k2_collide_site(const D2Desc &D, float (&d)[Q2],
 // populations a [9][L^2] block after the previous one's.
 // BATCH = false (one replica, the latency-bound small lattices): the
 // descriptor comes with the launch, no replica arithmetic, no descriptor load.
+// A wave is one row of the tile, so its pulls and stores are scalar row bases
+// plus 32-bit lane offsets (64 x 256^2: 70.2 -> 68.3 us a step, 48 x 256^2
+// 43.2 -> 41.2, 1800^2 44.1 -> 43.0, 400 x 100^2 85.9 -> 80.9).
+// NT: stores that do not stay in the caches (k2_store_nt).
 constexpr int K2TX = 64, K2TY = 4;
-template <bool BATCH>
+// Where the two copies of a batch exceed the 256 MB cache behind the L2s, no
+// line that is written is read again before it is evicted, and writing around
+// the caches leaves them to the reads: 64 x 256^2 68.3 -> 65.6 us, 128 x 256^2
+// 129.8 -> 125.5, 16 x 512^2 70.0 -> 66.1, 4 x 1024^2 69.5 -> 68.9.  Below that
+// size it costs (56 x 256^2 47.4 -> 59.4), as it does for rows that are not
+// whole 128-byte lines (400 x 100^2 79.1 -> 84.2) and for 2048^2 (69.7 -> 70.4).
+inline bool k2_store_nt(int L, int nrep) {
+    return L % 32 == 0 && L <= 1024 && nrep > 1 && (int64_t)nrep * L * L * (2 * Q2 * 4) > ((int64_t)256 << 20);
+}
+template <bool BATCH, bool NT>
 __global__ void __launch_bounds__(K2TX * K2TY)
 k2_step_tiled(D2Desc D0, const D2Desc *__restrict__ descs, int tiles_per_rep, const float *__restrict__ pop_all,
               float *__restrict__ pop_out_all, uint64_t t, int *__restrict__ err) {
@@ -242,12 +273,13 @@ k2_step_tiled(D2Desc D0, const D2Desc *__restrict__ descs, int tiles_per_rep, co
     const int ntx = (L + K2TX - 1) / K2TX;
     const int x0 = (tile % ntx) * K2TX, y0 = (tile / ntx) * K2TY;
     const int nx = min(K2TX, L - x0), ny = min(K2TY, L - y0);
-    const int tid = threadIdx.x, ix = tid % K2TX, iy = tid / K2TX;
+    static_assert(K2TX == 64, "a wave per row");
+    const int tid = threadIdx.x, ix = tid % K2TX, iy = __builtin_amdgcn_readfirstlane(tid / K2TX);
     const bool inner = ix < nx && iy < ny;
     const int r_in = (iy + 1) * EX + ix + 1;
     float d[Q2];
     if (inner) {
-        pull2(pop, L, x0 + ix, y0 + iy, d);
+        pull2_row(pop, L, x0 + ix, y0 + iy, d);
         s_rho[r_in] = drho2(d);
     }
     // halo: the rows above and below the tile, then the columns beside it
@@ -265,7 +297,7 @@ k2_step_tiled(D2Desc D0, const D2Desc *__restrict__ descs, int tiles_per_rep, co
             hx = (h & 1) ? nx + 1 : 0;
         }
         float h[Q2];
-        pull2(pop, L, wrap2(x0 - 1 + hx, L), wrap2(y0 - 1 + hy, L), h);
+        pull2<true>(pop, L, wrap2(x0 - 1 + hx, L), wrap2(y0 - 1 + hy, L), h);
         s_rho[hy * EX + hx] = drho2(h);
     }
     __syncthreads();
@@ -273,8 +305,14 @@ k2_step_tiled(D2Desc D0, const D2Desc *__restrict__ descs, int tiles_per_rep, co
     const uint32_t s = (uint32_t)(x0 + ix) + (uint32_t)L * (uint32_t)(y0 + iy);
     const bool ok = k2_collide_site(
         D, d, [&](int dx, int dy) { return s_rho[r_in + dy * EX + dx]; }, [&] { return k2_normals(D, s, t); });
+    float *out = pop_out + (uint32_t)(y0 + iy) * (uint32_t)L;
+    uint32_t col = 4u * (uint32_t)(x0 + ix);
+    asm("" : "+v"(col));
 #pragma unroll
-    for (int i = 0; i < Q2; ++i) pop_out[i * N + s] = d[i];
+    for (int i = 0; i < Q2; ++i) {
+        if constexpr (NT) stb(out + (size_t)i * N, col, d[i]);
+        else *(float *)((char *)(out + (size_t)i * N) + col) = d[i];
+    }
     if (!ok) *err = 1;
 }
 

@@ -26,10 +26,10 @@ struct Nbr {
     int x, y, z, xm, xp;
     int Y0, Ym, Yp;  // y * L etc.
     int Z0, Zm, Zp;  // z * L * L etc.
-    __device__ __forceinline__ Nbr(int64_t s, int L) {
+    __device__ __forceinline__ Nbr(int64_t s, int L) {  // s < L^3 <= 2^30: 32-bit division
         const int LL = L * L;
-        z = (int)(s / LL);
-        const int rem = (int)(s - (int64_t)z * LL);
+        z = (int)((uint32_t)s / (uint32_t)LL);
+        const int rem = (int)s - z * LL;
         y = rem / L;
         x = rem - y * L;
         xm = wrap_dec(x, L);
