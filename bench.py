@@ -54,7 +54,7 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-STEP_KERNEL_SOURCES = ("lbfss_device.hpp", "lbfss_step.hpp", "lbfss_fused.hpp")
+STEP_KERNEL_SOURCES = ("lbfss_device.hpp", "lbfss_step.hpp", "lbfss_fused.hpp", "lbfss_block.hpp")
 
 
 def code_of(text):
@@ -74,6 +74,16 @@ def kernel_source_hash(csrc=None, names=STEP_KERNEL_SOURCES):
         with open(os.path.join(csrc, name)) as fh:
             h.update(code_of(fh.read()).encode())
     return h.hexdigest()[:16]
+
+
+def force_step_kernel(plan):
+    """The kernel that updates the populations under a plan of the force
+    model: shallow tiles run the block kernel whatever the plan's name, the
+    split plan's collide pass is the block kernel too."""
+    blocks = ((16, 8, 1), (16, 8, 4), (32, 8, 4))
+    if plan["kernel"] == 0 or (plan["tile_x"], plan["tile_y"], plan["tile_z"]) in blocks:
+        return "k_block"
+    return "k_fused" if plan["kernel"] == 1 else "k_fused_staged"
 
 
 def read_traffic(kname, workload, storage, plan):
@@ -207,7 +217,7 @@ def main():
     ms_per_launch = e0.elapsed_time(e1) / nk
     algo_bytes = BYTES_PER_SITE[args.storage] * N
     achieved = algo_bytes / (ms_per_launch * 1e-3) / 1e9
-    kname = {0: "k_collide", 1: "k_fused", 2: "k_fused_staged", 3: "k_fused_staged"}[kplan["kernel"]]
+    kname = force_step_kernel(kplan)
     log(f"[bench] {kname}: {ms_per_launch * 1e3:.1f} us per step, {achieved:.0f} GB/s algorithmic")
     traffic = read_traffic(kname, args.workload, args.storage, kplan)
     del ksim
@@ -266,12 +276,13 @@ PAPER_MODEL_SOURCES = {"eq": ("lbfss_device.hpp", "lbfss_step.hpp", "lbfss_fused
                        "d2q9": ("lbfss_device.hpp", "lbfss_fused.hpp", "lbfss_d2q9.hpp")}
 
 
-def paper_model_kernels(model, plan):
-    """The kernels of one step of the paper's model under a plan."""
+def paper_model_kernels(model, plan, L=None):
+    """The kernels of one step of the paper's model under a plan (D2Q9: on a
+    lattice of edge L; up to 512^2 a launch takes two or three steps)."""
     if model == "d2q9":
-        return ("k2_step_tiled",)
+        return ("k2_steps_fused",) if L is not None and L <= 512 else ("k2_step_tiled",)
     if plan["kernel"] == 3:
-        return ("k_meq_staged",)
+        return ("k_block",) if (plan["tile_x"], plan["tile_y"]) == (32, 8) and plan["tile_z"] <= 2 else ("k_meq_staged",)
     return ("k_density", "k_meq_collide")
 
 
@@ -302,7 +313,7 @@ def bench_paper_model(args, wl, torch, lbf, workloads, stream):
     """The paper's own model (GL pressure in the equilibrium, noise with the
     local sound speed): on D3Q19 (LB_EQ_PRESSURE; the rows kernel
     k_meq_staged or the density and collide passes) or on D2Q9 (the lb2_*
-    calls: one tiled kernel per step).  The roofline is taken over the
+    calls: one tiled kernel, of one to three steps).  The roofline is taken over the
     step's kernels with the step's algorithmic bytes (populations read once
     and written once: 152 B per D3Q19 site, 72 B per D2Q9 site)."""
     model = wl.pop("model")
@@ -338,7 +349,7 @@ def bench_paper_model(args, wl, torch, lbf, workloads, stream):
             sim.tune(steps=10)
         plan = sim.plan()
         log(f"[bench] plan {plan}")
-    kernels = paper_model_kernels(model, plan)
+    kernels = paper_model_kernels(model, plan, L)
     sim.step(args.warmup)
     sim.sync()
     torch.cuda.synchronize()
@@ -386,7 +397,7 @@ def bench_paper_model(args, wl, torch, lbf, workloads, stream):
         "data": "synthetic",
         "config": {"workload": name, "L": L, "sites": N, "storage": "fp32", "sample_every": every,
                    "params": {k: wl[k] for k in ("a", "b", "kappa", "rho_c", "kT", "tau")},
-                   "plan": plan if plan is not None else "one tiled pass (64 x 4 sites per workgroup)"},
+                   "plan": plan if plan is not None else f"{kernels[0]}, no plan to choose"},
         "roofline": {"bound": "hbm", "kernel": " + ".join(kernels), "achieved": round(achieved, 1),
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": read_step_traffic(model, args.workload, kernels, plan), "bytes_per_site": bps,
