@@ -762,16 +762,16 @@ lb_plan default_plan(const lb_sim *s) {
         if (n <= 256) return lb_plan{march, 16, 8, 1, 0, 0};
         // deeper blocks where the lattice's edge leaves few of their threads
         // idle: 48^3 12.1 against 15.2 in two passes (40^3, padded by a
-        // fifth: 13.4 against 11.8), 64^3 15.8 against 16.2 (FP16 13.5, 15.9)
+        // fifth: 13.4 against 11.4), 64^3 15.4 against 16.2 (FP16 13.5, 15.9)
         for (int tx : {16, 32}) {
             count_tiles(s, tx, 8, 4, &n, &span);
             if (n <= 256 && 5 * span < 6 * T) return lb_plan{march, tx, 8, 4, 0, 0};
         }
         // two passes read the populations twice, but every CU is at work:
-        // 96^3 41 against 51 on the best marching tiles, 144^3 150 against
+        // 96^3 38 against 51 on the best marching tiles, 144^3 147 against
         // 156, 160^3 192 against 198, 176^3 279 against 237; FP16 112^3 54
         // against 58, 128^3 69 against 60.  Without rows staging (an edge
-        // that is no multiple of 4, FP16 of 8) they stay ahead: 250^3 859
+        // that is no multiple of 4, FP16 of 8) they stay ahead: 250^3 844
         // against 1183.  A batch of small lattices marches from 2^21 sites
         // (96-replica sweep: 130 against 139).
         const int64_t two = fp16 ? 116 * 116 * 116 : (maxL < 128 ? 128 * 128 * 128 : 161 * 161 * 161);
@@ -1359,7 +1359,8 @@ int lb_set_plan(lb_sim *s, const lb_plan *plan) {
     } else if (p.kernel != LB_KERNEL_SPLIT) {
         return LB_EINVAL;
     } else if (!s->eq_pressure) {  // the collide pass has tiles of its own
-        if (int rc = build_tiles(s, kSplitTX, kSplitTY, kSplitTZ)) return rc;
+        const bool flat = split_flat(s->storage == LB_FP16, s->total_sites);
+        if (int rc = build_tiles(s, kSplitTX, flat ? 8 : 4, flat ? 2 : 4)) return rc;
     }
     if (p.kernel != s->plan.kernel || p.tile_x != s->plan.tile_x || p.tile_y != s->plan.tile_y ||
         p.tile_z != s->plan.tile_z || p.graph_steps != s->plan.graph_steps)

@@ -222,9 +222,14 @@ inline bool block_tile(bool eq, int tx, int ty, int tz) {
     if (eq) return tx == 32 && ty == 8 && tz <= 2;
     return (tx == 16 && ty == 8 && (tz == 1 || tz == 4)) || (tx == 32 && ty == 8 && tz == 4);
 }
-// Tiles of the split plan's collide pass: 32-wide rows (250^3 FP32: 859 us a
-// step, 979 us on 16 x 8 x 4; the same at 64^3 and 96^3).
-constexpr int kSplitTX = 32, kSplitTY = 8, kSplitTZ = 2;
+// Blocks of the split plan's collide pass: 32-wide rows (16 x 8 x 4 takes 979
+// us a step at 250^3 FP32), 4 x 4 of them, which need the fewest halo rows of
+// the density: FP16 100^3 41.5 against 45.4 us on 8 x 2 rows, 250^3 537 against
+// 549; FP32 50^3 14.6 against 14.95, 178^3 306 against 317.  On large FP32
+// lattices the y neighbours' rows in the L2 count for more: 198^3 424 on 8 x 2
+// against 425, 226^3 628 against 635, 250^3 844 against 853.
+constexpr int kSplitTX = 32;
+inline bool split_flat(bool fp16, int64_t sites) { return !fp16 && sites >= 190 * 190 * 190; }
 
 struct BlockArgs {
     const RepDesc *desc;
@@ -265,7 +270,8 @@ inline void launch_block_eq(const BlockArgs &a, int tz, const float *in, float *
 // the collide pass of the split plan
 template <typename T>
 void launch_block_split(const BlockArgs &a, const T *in, T *out, const float *drho) {
-    launch_block_shape<kSplitTX, kSplitTY, kSplitTZ, 512, false, true>(a, in, out, drho);
+    if (split_flat(sizeof(T) == 2, a.total)) launch_block_shape<kSplitTX, 8, 2, 512, false, true>(a, in, out, drho);
+    else launch_block_shape<kSplitTX, 4, 4, 512, false, true>(a, in, out, drho);
 }
 
 }  // namespace lbfss
