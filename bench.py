@@ -54,7 +54,7 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-STEP_KERNEL_SOURCES = ("lbfss_device.hpp", "lbfss_step.hpp", "lbfss_fused.hpp", "lbfss_block.hpp")
+STEP_KERNEL_SOURCES = ("lbfss_device.hpp", "lbfss_step.hpp", "lbfss_fused.hpp")
 
 
 def code_of(text):
