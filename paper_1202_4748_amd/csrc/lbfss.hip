@@ -712,7 +712,7 @@ int build_sk3(lb_sim *s) {
 
 int build_tiles(lb_sim *s, int tx, int ty, int tz) {
     std::vector<FusedTile> tiles;
-    if (make_fused_tiles(s->hdesc, tx, ty, tz, tiles) != 0) return LB_EINVAL;
+    if (make_fused_tiles(s->L, tx, ty, tz, tiles) != 0) return LB_EINVAL;
     if (s->d_tiles && s->tiles_for[0] == tx && s->tiles_for[1] == ty && s->tiles_for[2] == tz) return LB_OK;
     if (s->d_tiles) {
         // the old table may still be read by queued kernels and captured graphs

@@ -23,13 +23,10 @@
 #include <array>
 #include <vector>
 
+#include "lbfss_plan.hpp"
 #include "lbfss_step.hpp"
 
 namespace lbfss {
-
-struct FusedTile {
-    int32_t rep, x0, y0, z0, nx, ny, nz, pad;
-};
 
 __device__ __forceinline__ int wrap_near(int v, int L) { return v < 0 ? v + L : (v >= L ? v - L : v); }
 
@@ -667,50 +664,10 @@ k_fused_staged(const RepDesc *__restrict__ desc, const FusedTile *__restrict__ t
 }
 
 // ---------------------------------------------------------------------------
-// Host side: tile tables and launch.
+// Host side: launch.
 // ---------------------------------------------------------------------------
 inline bool fused_tile_ok(int tx, int ty) {
     return (tx == 16 && ty == 16) || (tx == 32 && ty == 8) || (tx == 16 && ty == 8) || (tx == 64 && ty == 4);
-}
-
-// The tile table of a plan: x fastest, then y, then z, which xcd_tile deals to
-// the XCDs in contiguous runs.  Replicas of a batch are dealt whole, the
-// largest first, each to the XCD with the least work so far, and the shorter
-// lists are filled with empty tiles: with one run over all replicas some XCDs
-// held only tiles of the large lattices and finished last (96-replica sweep on
-// 32 x 8 x 12: 136 us a step in order, 130 us dealt).
-inline int make_fused_tiles(const std::vector<RepDesc> &reps, int tx, int ty, int tz,
-                            std::vector<FusedTile> &out) {
-    if (tx < 1 || ty < 1 || tz < 1 || tz > 1024) return -1;
-    constexpr int NX = 8;  // XCDs
-    out.clear();
-    std::vector<size_t> order(reps.size());
-    for (size_t r = 0; r < reps.size(); ++r) order[r] = r;
-    std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return reps[a].L > reps[b].L; });
-    std::array<std::vector<FusedTile>, NX> lists;
-    std::array<int64_t, NX> work{};
-    const int n_lists = reps.size() > 1 ? NX : 1;
-    for (size_t r : order) {
-        const int L = reps[r].L;
-        const int nx = std::min(tx, L), ny = std::min(ty, L), nz = std::min(tz, L);
-        const int k = (int)(std::min_element(work.begin(), work.begin() + n_lists) - work.begin());
-        for (int z0 = 0; z0 < L; z0 += nz)
-            for (int y0 = 0; y0 < L; y0 += ny)
-                for (int x0 = 0; x0 < L; x0 += nx) {
-                    lists[k].push_back(FusedTile{(int32_t)r, x0, y0, z0, std::min(nx, L - x0), std::min(ny, L - y0),
-                                                 std::min(nz, L - z0), 0});
-                    work[k] += lists[k].back().nz + 4;  // planes marched
-                }
-    }
-    if (n_lists == 1) {
-        out = std::move(lists[0]);
-        return 0;
-    }
-    size_t per = 0;
-    for (const auto &l : lists) per = std::max(per, l.size());
-    out.assign(per * NX, FusedTile{0, 0, 0, 0, 0, 0, 0, 0});
-    for (int k = 0; k < NX; ++k) std::copy(lists[k].begin(), lists[k].end(), out.begin() + per * k);
-    return 0;
 }
 
 inline std::vector<std::array<int, 3>> fused_tile_candidates(const std::vector<RepDesc> &reps, bool eq) {

@@ -1,0 +1,78 @@
+// Host side of the launch plans: the tile table of a plan (plain C++, no HIP).
+#pragma once
+
+#include <algorithm>
+#include <array>
+#include <cstdint>
+#include <numeric>
+#include <vector>
+
+namespace lbfss {
+
+struct FusedTile {
+    int32_t rep, x0, y0, z0, nx, ny, nz, pad;
+};
+
+constexpr int kXcds = 8;
+
+// The tile table of a plan over replicas of edges Ls: of one replica x
+// fastest, then y, then z, which xcd_tile deals to the XCDs in contiguous
+// runs.  For a batch the table holds a list per XCD, the shorter lists filled
+// with empty tiles (nz = 0).  Replicas, the largest first, go whole to the XCD
+// with the least work so far where that leaves the fullest one within 5% of
+// the even share (96-replica sweep on 32 x 8 x 12: 136 us a step with its
+// tiles in one run, 130 us dealt whole); where it does not, the lists are runs
+// of equal work over all tiles, cut where they end (2 x 256^3: whole replicas
+// would keep two XCDs of eight, 3597 us a step against 1247 in one run).
+inline int make_fused_tiles(const std::vector<int> &Ls, int tx, int ty, int tz, std::vector<FusedTile> &out) {
+    if (tx < 1 || ty < 1 || tz < 1 || tz > 1024) return -1;
+    out.clear();
+    std::vector<size_t> order(Ls.size());
+    std::iota(order.begin(), order.end(), size_t(0));
+    std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return Ls[a] > Ls[b]; });
+    auto work_of = [](const FusedTile &t) { return (int64_t)t.nz + 4; };  // planes marched
+    std::vector<FusedTile> run;  // all tiles in order
+    std::vector<size_t> ends;    // of each replica's tiles there
+    int64_t total = 0;
+    for (size_t r : order) {
+        const int L = Ls[r], nx = std::min(tx, L), ny = std::min(ty, L), nz = std::min(tz, L);
+        for (int z0 = 0; z0 < L; z0 += nz)
+            for (int y0 = 0; y0 < L; y0 += ny)
+                for (int x0 = 0; x0 < L; x0 += nx) {
+                    run.push_back(FusedTile{(int32_t)r, x0, y0, z0, std::min(nx, L - x0), std::min(ny, L - y0),
+                                            std::min(nz, L - z0), 0});
+                    total += work_of(run.back());
+                }
+        ends.push_back(run.size());
+    }
+    if (Ls.size() < 2) {
+        out = std::move(run);
+        return 0;
+    }
+    std::array<std::vector<FusedTile>, kXcds> lists;
+    std::array<int64_t, kXcds> work{};
+    size_t first = 0;
+    for (size_t end : ends) {
+        const int k = (int)(std::min_element(work.begin(), work.end()) - work.begin());
+        for (; first < end; ++first) {
+            lists[k].push_back(run[first]);
+            work[k] += work_of(run[first]);
+        }
+    }
+    if (20 * kXcds * *std::max_element(work.begin(), work.end()) > 21 * total) {
+        for (auto &l : lists) l.clear();
+        int64_t before = 0;
+        for (const FusedTile &t : run) {  // by the middle of the tile's share of the run
+            const int64_t w = work_of(t);
+            lists[(2 * before + w) * kXcds / (2 * total)].push_back(t);
+            before += w;
+        }
+    }
+    size_t per = 0;
+    for (const auto &l : lists) per = std::max(per, l.size());
+    out.assign(per * kXcds, FusedTile{0, 0, 0, 0, 0, 0, 0, 0});
+    for (int k = 0; k < kXcds; ++k) std::copy(lists[k].begin(), lists[k].end(), out.begin() + per * k);
+    return 0;
+}
+
+}  // namespace lbfss
