@@ -710,20 +710,27 @@ int build_sk3(lb_sim *s) {
     return LB_OK;
 }
 
+// The table of a plan, in place of the one before.  The new table is there
+// before the old one goes: every plan of the force model reads a table, so a
+// handle whose plan cannot be changed for want of memory keeps its own.
 int build_tiles(lb_sim *s, int tx, int ty, int tz) {
     std::vector<FusedTile> tiles;
     if (make_fused_tiles(s->L, tx, ty, tz, tiles) != 0) return LB_EINVAL;
     if (s->d_tiles && s->tiles_for[0] == tx && s->tiles_for[1] == ty && s->tiles_for[2] == tz) return LB_OK;
-    if (s->d_tiles) {
-        // the old table may still be read by queued kernels and captured graphs
-        HIPCHK(hipStreamSynchronize(s->stream));
-        drop_graph(s);
-        dev_release(s, s->d_tiles, sizeof(FusedTile) * std::max<size_t>((size_t)s->n_tiles, 1));
-        s->d_tiles = nullptr;
-        s->n_tiles = 0;
+    FusedTile *fresh = nullptr;
+    const size_t bytes = sizeof(FusedTile) * tiles.size();
+    int rc = upload(s, &fresh, tiles);
+    // the old table may still be read by queued kernels and captured graphs
+    if (rc == LB_OK && s->d_tiles && hipStreamSynchronize(s->stream) != hipSuccess) rc = LB_EDEVICE;
+    if (rc) {
+        dev_release(s, fresh, bytes);
+        return rc;
     }
-    int rc = upload(s, &s->d_tiles, tiles);
-    if (rc) return rc;
+    if (s->d_tiles) {
+        drop_graph(s);
+        dev_release(s, s->d_tiles, sizeof(FusedTile) * (size_t)s->n_tiles);
+    }
+    s->d_tiles = fresh;
     s->n_tiles = (int)tiles.size();
     s->tiles_for[0] = tx;
     s->tiles_for[1] = ty;
