@@ -38,12 +38,28 @@ class HostStage {
     hipError_t to_device(void *dst, const void *src, size_t bytes) { return move((char *)src, (char *)dst, bytes, false); }
 
   private:
+    struct OnDevice {
+        int was = -1;
+        hipError_t err;
+        explicit OnDevice(int device) {
+            err = hipGetDevice(&was);
+            if (err == hipSuccess && was != device) err = hipSetDevice(device);
+            else was = -1;
+        }
+        ~OnDevice() {
+            if (was >= 0) (void)hipSetDevice(was);
+        }
+    };
     hipError_t plain(char *host, char *dev, size_t bytes, bool down) {
         return down ? hipMemcpyAsync(host, dev, bytes, hipMemcpyDeviceToHost, stream_)
                     : hipMemcpyAsync(dev, host, bytes, hipMemcpyHostToDevice, stream_);
     }
     hipError_t move(char *host, char *dev, size_t bytes, bool down) {
         if (bytes < kStagedMin) return plain(host, dev, bytes, down);
+        // the buffers and the first worker's events are the stream's device's,
+        // whichever is current on the caller's thread
+        OnDevice on(device_);
+        if (on.err != hipSuccess) return on.err;
         if (!pin_ && hipHostMalloc((void **)&pin_, 2 * kStageWorkers * kStagePiece, hipHostMallocDefault) != hipSuccess) {
             pin_ = nullptr;
             (void)hipGetLastError();
