@@ -326,7 +326,8 @@ typedef __attribute__((address_space(3))) void *lptr_t;
 // the first LDS read that may see it, draining the population stores as
 // well; the kernels count the operations themselves (vmcnt_wait).  The copy
 // has no output register, reads its address as it issues, and needs one wait
-// state after the write of M0.  With the copies in flight through the
+// state after the write of M0, which is left to the compiler (an operand, so
+// that it knows what M0 holds).  With the copies in flight through the
 // collision and the stores through the next wait: 512^3 FP32 5170 -> 4920 us
 // a step, 512^3 FP16 4.04 -> 3.85 ms, the paper's model at 256^3 577 -> 551.
 template <int BYTES>
@@ -334,11 +335,9 @@ __device__ __forceinline__ void copy_to_lds(const void *g, lptr_t dst) {
     static_assert(BYTES == 16 || BYTES == 4, "copy widths in use");
     const uint32_t base = (uint32_t)(uintptr_t)dst;
     if constexpr (BYTES == 16)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(base), "v"(g)
-                     : "memory");
+        asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"{m0}"(base), "v"(g) : "memory");
     else
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(base), "v"(g)
-                     : "memory");
+        asm volatile("s_nop 0\n\tglobal_load_lds_dword %1, off" ::"{m0}"(base), "v"(g) : "memory");
 }
 
 __device__ __forceinline__ uint32_t pull_off(int q, const PlaneOffs &o) {
