@@ -6,7 +6,8 @@
 // threads moving the pieces between them and the caller's memory while the
 // next ones are on the bus: 30 GB/s on four threads (134 MB 12.3 -> 4.4 ms,
 // 50 MB 4.6 -> 1.7 ms, 8 MB 0.78 -> 0.43 ms; two threads 22 GB/s, eight as
-// four).  Below kStagedMin the threads cost what they save.  The buffers live
+// four).  Below kStagedMin the threads cost what they save, and memory that is
+// pinned already needs none of it.  The buffers live
 // for one call (allocating them takes 0.12 ms).
 #pragma once
 
@@ -50,12 +51,21 @@ class HostStage {
             if (was >= 0) (void)hipSetDevice(was);
         }
     };
+    // Memory that the runtime knows (pinned, managed, a device's) it copies in
+    // one piece and faster, 45 to 56 GB/s: 128^3 density into a pinned array
+    // 0.37 ms, through the pieces 0.78 ms; 192^3 populations 19.1, 35.9 ms.
+    static bool known(const void *p) {
+        hipPointerAttribute_t a{};
+        if (hipPointerGetAttributes(&a, p) == hipSuccess) return a.type != hipMemoryTypeUnregistered;
+        (void)hipGetLastError();
+        return false;
+    }
     hipError_t plain(char *host, char *dev, size_t bytes, bool down) {
         return down ? hipMemcpyAsync(host, dev, bytes, hipMemcpyDeviceToHost, stream_)
                     : hipMemcpyAsync(dev, host, bytes, hipMemcpyHostToDevice, stream_);
     }
     hipError_t move(char *host, char *dev, size_t bytes, bool down) {
-        if (bytes < kStagedMin) return plain(host, dev, bytes, down);
+        if (bytes < kStagedMin || known(host)) return plain(host, dev, bytes, down);
         // the buffers and the first worker's events are the stream's device's,
         // whichever is current on the caller's thread
         OnDevice on(device_);

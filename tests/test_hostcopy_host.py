@@ -16,6 +16,8 @@ RUNTIME = r"""
 #include <cstdlib>
 #include <cstring>
 enum hipError_t { hipSuccess = 0, hipErrorInvalidResourceHandle = 400, hipErrorOutOfMemory = 2 };
+enum hipMemoryType { hipMemoryTypeUnregistered = 0, hipMemoryTypeHost = 1 };
+struct hipPointerAttribute_t { hipMemoryType type; };
 enum hipMemcpyKind { hipMemcpyHostToDevice, hipMemcpyDeviceToHost };
 constexpr unsigned hipHostMallocDefault = 0, hipEventDisableTiming = 2;
 struct Event { int device; };
@@ -27,6 +29,11 @@ inline std::atomic<int> g_fail_copy{-1};  // the copy that fails
 inline hipError_t hipGetDevice(int *d) { *d = g_current; return hipSuccess; }
 inline hipError_t hipSetDevice(int d) { g_current = d; return hipSuccess; }
 inline hipError_t hipGetLastError() { return hipSuccess; }
+inline std::atomic<int> g_known{0};  // -1: the runtime has no answer
+inline hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *) {
+    a->type = g_known > 0 ? hipMemoryTypeHost : hipMemoryTypeUnregistered;
+    return g_known < 0 ? hipErrorInvalidResourceHandle : hipSuccess;
+}
 inline hipError_t hipHostMalloc(void **p, size_t n, unsigned) { ++g_pinned; *p = malloc(n); return hipSuccess; }
 inline hipError_t hipHostFree(void *p) { --g_pinned; free(p); return hipSuccess; }
 inline hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
@@ -47,11 +54,12 @@ PROGRAM = r"""
 #include <cstdio>
 #include <vector>
 #include "lbfss_hostcopy.hpp"
-int main(int argc, char **argv) {  // current device, down, bytes, the copy that fails
+int main(int argc, char **argv) {  // current device, down, bytes, the copy that fails, known
     g_current = atoi(argv[1]);
     const bool down = atoi(argv[2]);
     const size_t n = atol(argv[3]);
     g_fail_copy = atoi(argv[4]);
+    g_known = atoi(argv[5]);
     std::vector<unsigned char> host(n), dev(n);
     for (size_t i = 0; i < n; ++i) (down ? dev : host)[i] = (unsigned char)(i * 2654435761u >> 24);
     hipError_t e;
@@ -59,7 +67,7 @@ int main(int argc, char **argv) {  // current device, down, bytes, the copy that
         lbfss::HostStage stage(1, 1);
         e = down ? stage.to_host(host.data(), dev.data(), n) : stage.to_device(dev.data(), host.data(), n);
     }
-    printf("%d %d %d %d %d\n", (int)e, host == dev, g_current, g_pinned.load(), g_events.load());
+    printf("%d %d %d %d %d %d\n", (int)e, host == dev, g_current, g_pinned.load(), g_events.load(), g_copies.load());
 }
 """
 
@@ -73,9 +81,9 @@ def copy(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-I", str(d), "-I",
                     os.path.join(ROOT, "paper_1202_4748_amd", "csrc"), "-o", str(d / "t"), str(d / "t.cpp")], check=True)
 
-    def run(current, down, n, fail=-1):
-        r = subprocess.run([str(d / "t"), str(current), str(int(down)), str(n), str(fail)], capture_output=True,
-                           text=True, check=True, timeout=60)
+    def run(current, down, n, fail=-1, known=0):
+        r = subprocess.run([str(d / "t"), str(current), str(int(down)), str(n), str(fail), str(known)],
+                           capture_output=True, text=True, check=True, timeout=60)
         return tuple(map(int, r.stdout.split()))
 
     return run
@@ -86,11 +94,19 @@ def copy(tmp_path_factory):
 @pytest.mark.parametrize("current", [0, 1])
 def test_copies_with_any_device_current(copy, current, n, down):
     """No error, the data, the caller's device as it was, nothing left over."""
-    assert copy(current, down, n) == (0, 1, current, 0, 0)
+    assert copy(current, down, n)[:5] == (0, 1, current, 0, 0)
 
 
 @pytest.mark.parametrize("down", [False, True])
 @pytest.mark.parametrize("current", [0, 1])
 def test_a_failed_piece_is_reported(copy, current, down):
-    err, _, dev, pinned, events = copy(current, down, 20 << 20, 5)
+    err, _, dev, pinned, events, _ = copy(current, down, 20 << 20, 5)
     assert (err, dev, pinned, events) == (400, current, 0, 0)
+
+
+@pytest.mark.parametrize("down", [False, True])
+def test_memory_the_runtime_knows_goes_in_one_copy(copy, down):
+    """Pinned arrays of the caller are not passed through the pieces; memory
+    that the runtime has no answer for is taken for ordinary memory."""
+    assert copy(0, down, 20 << 20, known=1) == (0, 1, 0, 0, 0, 1)
+    assert copy(0, down, 20 << 20, known=0) == copy(0, down, 20 << 20, known=-1) == (0, 1, 0, 0, 0, 20)
