@@ -1713,9 +1713,10 @@ int lb2_step(lb2_sim *s, int64_t n) {
     const int tiles = (int)(ceil_div(s->L, K2TX) * ceil_div(s->L, K2TY));
     const int ftiles = (int)(ceil_div(s->L, K2F_T) * ceil_div(s->L, K2F_T));
     const unsigned R = (unsigned)s->nrep;
-    const auto one_step = k2_store_nt(s->L, s->nrep) ? &k2_step_tiled<true, true>
-                          : s->nrep > 1              ? &k2_step_tiled<true, false>
-                                                     : &k2_step_tiled<false, false>;
+    const bool rows = k2_row_bases(s->L, s->nrep);
+    const auto one_step = k2_store_nt(s->L, s->nrep) ? &k2_step_tiled<true, true, true>
+                          : s->nrep > 1 ? (rows ? &k2_step_tiled<true, true, false> : &k2_step_tiled<true, false, false>)
+                                        : (rows ? &k2_step_tiled<false, true, false> : &k2_step_tiled<false, false, false>);
     while (n > 0) {
         const int64_t e = s->sample_every;
         const int64_t left = e > 0 ? std::min<int64_t>(n, e - s->t % e) : n;
@@ -1723,8 +1724,8 @@ int lb2_step(lb2_sim *s, int64_t n) {
         float *out = s->pop[s->cur ^ 1];
         const int K = k2_steps_per_launch(s, left);
         if (K == 1)
-            hipLaunchKernelGGL(one_step, dim3((unsigned)tiles * R), dim3(K2TX * K2TY), 0, s->stream, s->D[0], (const D2Desc *)s->d_desc, tiles, in, out,
-                               (uint64_t)s->t, s->d_err);
+            hipLaunchKernelGGL(one_step, dim3((unsigned)tiles * R), dim3(K2TX * K2TY), 0, s->stream, s->D[0],
+                               (const D2Desc *)s->d_desc, tiles, in, out, (uint64_t)s->t, s->d_err);
         else if (K == 2)
             hipLaunchKernelGGL(k2_steps_fused<2>, dim3((unsigned)ftiles * R), dim3(K2Fused<2>::NT), 0, s->stream,
                                (const D2Desc *)s->d_desc, ftiles, in, out, (uint64_t)s->t, s->d_err);

@@ -60,10 +60,10 @@ __device__ __forceinline__ int wrap2(int v, int L) { return v < 0 ? v + L : (v >
 // Pulled deviations of site (x, y): d_i(r - c_i).  The three source columns
 // x - c_x and the three source rows y - c_y are wrapped once; each pull is
 // then a 32-bit in-plane offset from the population's (uniform) base.
-// MUL24: the rows' offsets by the full-rate 24-bit multiply (L <= 2048), which
-// the one-step kernel's halo gains from (1000^2 16.4 -> 16.05 us a step, 400 x
-// 100^2 81.9 -> 80.9; 700^2 9.13 -> 9.20) and
-// the kernels of several steps do not (512^2 5.62 -> 5.75).
+// MUL24: the rows' offsets by the full-rate 24-bit multiply (L <= 2048), for
+// the halo of the one-step kernel's large launches (1000^2 16.4 -> 16.05 us a
+// step, 400 x 100^2 81.9 -> 80.9); the kernels of several steps lose by it
+// (512^2 5.62 -> 5.75).
 template <bool MUL24 = false>
 __device__ __forceinline__ void pull2(const float *__restrict__ pop, int L, int x, int y, float (&d)[Q2]) {
     const uint32_t N = (uint32_t)L * (uint32_t)L;
@@ -242,9 +242,10 @@ __device__ __forceinline__ bool k2_collide_site(const D2Desc &D, float (&d)[Q2],
 // populations a [9][L^2] block after the previous one's.
 // BATCH = false (one replica, the latency-bound small lattices): the
 // descriptor comes with the launch, no replica arithmetic, no descriptor load.
-// A wave is one row of the tile, so its pulls and stores are scalar row bases
-// plus 32-bit lane offsets (64 x 256^2: 70.2 -> 68.3 us a step, 48 x 256^2
-// 43.2 -> 41.2, 1800^2 44.1 -> 43.0, 400 x 100^2 85.9 -> 80.9).
+// ROWS: a wave is one row of the tile, so its pulls and stores are scalar row
+// bases plus 32-bit lane offsets (64 x 256^2: 70.2 -> 68.3 us a step, 48 x 256^2
+// 43.2 -> 41.2, 1800^2 44.1 -> 43.0, 400 x 100^2 85.9 -> 80.9), for launches
+// with work enough to hide the scalar chain that forms them (k2_row_bases).
 // NT: stores that do not stay in the caches (k2_store_nt).
 constexpr int K2TX = 64, K2TY = 4;
 // Where the two copies of a batch exceed the 256 MB cache behind the L2s, no
@@ -256,7 +257,16 @@ constexpr int K2TX = 64, K2TY = 4;
 inline bool k2_store_nt(int L, int nrep) {
     return L % 32 == 0 && L <= 1024 && nrep > 1 && (int64_t)nrep * L * L * (2 * Q2 * 4) > ((int64_t)256 << 20);
 }
-template <bool BATCH, bool NT>
+// The scalar row bases are a chain ahead of the first load, 0.3 us of a launch
+// whose workgroups all start at once: 7 x 256^2 8.32 -> 8.84 us, 20 x 128^2
+// 6.80 -> 7.24, 40 x 100^2 8.50 -> 8.74, 14 x 200^2 11.5 -> 11.7, 768^2 10.9 ->
+// 11.2, 850^2 12.8 -> 13.1 with them; 9 x 256^2 11.3 -> 11.1, 36 x 128^2 11.2 ->
+// 10.95, 16 x 200^2 12.9 -> 12.6, 900^2 14.4 -> 14.3, 1200^2 21.9 -> 21.5.  So
+// from nine full tiles a CU in a batch, twelve of one lattice.
+inline bool k2_row_bases(int L, int nrep) {
+    return (int64_t)nrep * L * L >= (int64_t)(nrep > 1 ? 9 : 12) * 256 * K2TX * K2TY;
+}
+template <bool BATCH, bool ROWS, bool NT>
 __global__ void __launch_bounds__(K2TX * K2TY)
 k2_step_tiled(D2Desc D0, const D2Desc *__restrict__ descs, int tiles_per_rep, const float *__restrict__ pop_all,
               float *__restrict__ pop_out_all, uint64_t t, int *__restrict__ err) {
@@ -274,12 +284,14 @@ k2_step_tiled(D2Desc D0, const D2Desc *__restrict__ descs, int tiles_per_rep, co
     const int x0 = (tile % ntx) * K2TX, y0 = (tile / ntx) * K2TY;
     const int nx = min(K2TX, L - x0), ny = min(K2TY, L - y0);
     static_assert(K2TX == 64, "a wave per row");
-    const int tid = threadIdx.x, ix = tid % K2TX, iy = __builtin_amdgcn_readfirstlane(tid / K2TX);
+    const int tid = threadIdx.x, ix = tid % K2TX;
+    const int iy = ROWS ? __builtin_amdgcn_readfirstlane(tid / K2TX) : tid / K2TX;
     const bool inner = ix < nx && iy < ny;
     const int r_in = (iy + 1) * EX + ix + 1;
     float d[Q2];
     if (inner) {
-        pull2_row(pop, L, x0 + ix, y0 + iy, d);
+        if constexpr (ROWS) pull2_row(pop, L, x0 + ix, y0 + iy, d);
+        else pull2(pop, L, x0 + ix, y0 + iy, d);
         s_rho[r_in] = drho2(d);
     }
     // halo: the rows above and below the tile, then the columns beside it
@@ -297,7 +309,7 @@ k2_step_tiled(D2Desc D0, const D2Desc *__restrict__ descs, int tiles_per_rep, co
             hx = (h & 1) ? nx + 1 : 0;
         }
         float h[Q2];
-        pull2<true>(pop, L, wrap2(x0 - 1 + hx, L), wrap2(y0 - 1 + hy, L), h);
+        pull2<ROWS>(pop, L, wrap2(x0 - 1 + hx, L), wrap2(y0 - 1 + hy, L), h);
         s_rho[hy * EX + hx] = drho2(h);
     }
     __syncthreads();
@@ -305,13 +317,19 @@ k2_step_tiled(D2Desc D0, const D2Desc *__restrict__ descs, int tiles_per_rep, co
     const uint32_t s = (uint32_t)(x0 + ix) + (uint32_t)L * (uint32_t)(y0 + iy);
     const bool ok = k2_collide_site(
         D, d, [&](int dx, int dy) { return s_rho[r_in + dy * EX + dx]; }, [&] { return k2_normals(D, s, t); });
-    float *out = pop_out + (uint32_t)(y0 + iy) * (uint32_t)L;
-    uint32_t col = 4u * (uint32_t)(x0 + ix);
-    asm("" : "+v"(col));
+    if constexpr (ROWS) {
+        float *out = pop_out + (uint32_t)(y0 + iy) * (uint32_t)L;
+        uint32_t col = 4u * (uint32_t)(x0 + ix);
+        asm("" : "+v"(col));
 #pragma unroll
-    for (int i = 0; i < Q2; ++i) {
-        if constexpr (NT) stb(out + (size_t)i * N, col, d[i]);
-        else *(float *)((char *)(out + (size_t)i * N) + col) = d[i];
+        for (int i = 0; i < Q2; ++i) {
+            if constexpr (NT) stb(out + (size_t)i * N, col, d[i]);
+            else *(float *)((char *)(out + (size_t)i * N) + col) = d[i];
+        }
+    } else {
+        static_assert(!NT, "such launches stay in the caches");
+#pragma unroll
+        for (int i = 0; i < Q2; ++i) pop_out[i * N + s] = d[i];
     }
     if (!ok) *err = 1;
 }
