@@ -138,6 +138,7 @@ struct lb_sim {
     FusedTile *d_tiles = nullptr;
     int n_tiles = 0;
     int tiles_for[3] = {0, 0, 0};
+    bool drain[2] = {false, false};  // staged steps without and with a snapshot: drained_plan
 
     int64_t t = 0;
     lb_plan plan{LB_KERNEL_SPLIT, 0, 0, 0, 0, 0};
@@ -285,16 +286,17 @@ void launch_step(lb_sim *s, int cur, int koff, float *snap) {
         launch_block<T>(blk, s->plan.tile_x, s->plan.tile_z, in, out);
         return;
     }
+    const StagedArgs staged{s->d_desc, s->d_tiles, s->n_tiles, s->d_step, koff, s->d_err, snap, total, s->stream};
+    const bool drain = s->drain[snap != nullptr];
     if (s->plan.kernel == LB_KERNEL_ROWS && s->n_tiles > 0) {
-        launch_fused_staged<T, true>(s->d_desc, s->d_tiles, s->n_tiles, in, out, s->d_step, koff, s->d_err,
-                                     s->plan.tile_x, s->plan.tile_y, s->stream, snap, total);
+        launch_fused_staged<T, true>(staged, s->plan.tile_x, s->plan.tile_y, drain, in, out);
         return;
     }
-    if (s->plan.kernel == LB_KERNEL_STAGED && s->n_tiles > 0 && std::is_same<T, float>::value) {
-        launch_fused_staged<float, false>(s->d_desc, s->d_tiles, s->n_tiles, (const float *)in, (float *)out,
-                                          s->d_step, koff, s->d_err, s->plan.tile_x, s->plan.tile_y, s->stream, snap,
-                                          total);
-        return;
+    if constexpr (std::is_same<T, float>::value) {
+        if (s->plan.kernel == LB_KERNEL_STAGED && s->n_tiles > 0) {
+            launch_fused_staged<float, false>(staged, s->plan.tile_x, s->plan.tile_y, drain, in, out);
+            return;
+        }
     }
     if (s->plan.kernel != LB_KERNEL_SPLIT && s->n_tiles > 0) {
         launch_fused<T>(s->d_desc, s->d_tiles, s->n_tiles, in, out, s->d_step, koff, s->d_err,
@@ -735,6 +737,8 @@ int build_tiles(lb_sim *s, int tx, int ty, int tz) {
     s->tiles_for[0] = tx;
     s->tiles_for[1] = ty;
     s->tiles_for[2] = tz;
+    for (int snap = 0; snap < 2; ++snap)
+        s->drain[snap] = drained_plan(s->L, s->storage == LB_FP16, tx, ty, s->n_tiles, snap != 0);
     return LB_OK;
 }
 

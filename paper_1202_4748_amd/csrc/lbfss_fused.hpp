@@ -373,13 +373,11 @@ __device__ __forceinline__ uint32_t pull_off(int q, const PlaneOffs &o) {
 // 625 against 620 us a step at 256^3 FP32 with a sample every ten, 5115 against
 // 4906 at 512^3.
 //
-// DRAIN: wait for the staged copies and the stores at every barrier, as
-// __syncthreads() would.  Where all tiles of the lattice are resident at once
-// this keeps neighbouring tiles in step, so that the halo rows one stages are
-// still in L2 when the next does: 256^3 FP32 on 64 x 8 x 64 (512 tiles on 256
-// CUs) 609 us a step drained, 628 us not; with more tiles than one round the
-// copies are better left in flight (512^3: 5240 us drained, 4920 us not).
-template <typename T, int TX, int TY, bool ROWS, bool SNAP, bool DRAIN = false>
+// DRAIN (drained_plan): wait for the staged copies and the stores at every
+// barrier, as __syncthreads() would.  It keeps neighbouring tiles in step, so
+// that the halo rows one stages are still in L2 when the next does.  (An
+// instance of its own: chosen at run time 256^3 FP32 takes 606 us for 600.)
+template <typename T, int TX, int TY, bool ROWS, bool SNAP, bool DRAIN>
 __global__ void __launch_bounds__(TX * TY)
 k_fused_staged(const RepDesc *__restrict__ desc, const FusedTile *__restrict__ tiles, const T *__restrict__ pop,
                T *__restrict__ pop_out, const uint64_t *__restrict__ step, int koff, int *__restrict__ err,
@@ -739,45 +737,37 @@ inline bool rows_tile_ok(int tx, int ty) {
     return staged_tile_ok(tx, ty) || (tx == 64 && ty == 4) || (tx == 64 && ty == 8);
 }
 
-// 64 x 8 tiles resident at once: two workgroups on each of 256 CUs
-constexpr int kOneRound = 512;
+struct StagedArgs {
+    const RepDesc *desc;
+    const FusedTile *tiles;
+    int n_tiles;
+    const uint64_t *step;
+    int koff;
+    int *err;
+    float *snap;  // as launch_fused
+    int64_t total;
+    hipStream_t stream;
+};
 
-template <typename T, bool ROWS, bool SNAP>
-void launch_staged_snap(const RepDesc *desc, const FusedTile *tiles, int n_tiles, const T *in, T *out,
-                        const uint64_t *step, int koff, int *err, int tx, int ty, hipStream_t stream, float *snap,
-                        int64_t total) {
-    if (tx == 16 && ty == 16)
-        hipLaunchKernelGGL((k_fused_staged<T, 16, 16, ROWS, SNAP>), dim3(n_tiles), dim3(256), 0, stream, desc, tiles,
-                           in, out, step, koff, err, snap, total);
-    else if (tx == 16 && ty == 8)
-        hipLaunchKernelGGL((k_fused_staged<T, 16, 8, ROWS, SNAP>), dim3(n_tiles), dim3(128), 0, stream, desc, tiles,
-                           in, out, step, koff, err, snap, total);
-    else if (ROWS && tx == 64 && ty == 4)
-        hipLaunchKernelGGL((k_fused_staged<T, 64, 4, true, SNAP>), dim3(n_tiles), dim3(256), 0, stream, desc, tiles,
-                           in, out, step, koff, err, snap, total);
-    else if (ROWS && tx == 64 && ty == 8) {
-        constexpr bool can_drain = sizeof(T) == 4 && !SNAP;
-        if (can_drain && n_tiles <= kOneRound)
-            hipLaunchKernelGGL((k_fused_staged<T, 64, 8, true, SNAP, can_drain>), dim3(n_tiles), dim3(512), 0, stream,
-                               desc, tiles, in, out, step, koff, err, snap, total);
-        else
-            hipLaunchKernelGGL((k_fused_staged<T, 64, 8, true, SNAP>), dim3(n_tiles), dim3(512), 0, stream, desc,
-                               tiles, in, out, step, koff, err, snap, total);
-    }
-    else
-        hipLaunchKernelGGL((k_fused_staged<T, 32, 8, ROWS, SNAP>), dim3(n_tiles), dim3(256), 0, stream, desc, tiles,
-                           in, out, step, koff, err, snap, total);
+template <typename T, bool ROWS, bool SNAP, bool DRAIN>
+void launch_staged_tile(const StagedArgs &a, int tx, int ty, const T *in, T *out) {
+#define LBFSS_LAUNCH_STAGED(TX_, TY_, ROWS_)                                                                         \
+    hipLaunchKernelGGL((k_fused_staged<T, TX_, TY_, ROWS_, SNAP, DRAIN>), dim3(a.n_tiles), dim3(TX_ * TY_), 0, \
+                       a.stream, a.desc, a.tiles, in, out, a.step, a.koff, a.err, a.snap, a.total)
+    if (tx == 16 && ty == 16) LBFSS_LAUNCH_STAGED(16, 16, ROWS);
+    else if (tx == 16 && ty == 8) LBFSS_LAUNCH_STAGED(16, 8, ROWS);
+    else if (ROWS && tx == 64 && ty == 4) LBFSS_LAUNCH_STAGED(64, 4, true);
+    else if (ROWS && tx == 64 && ty == 8) LBFSS_LAUNCH_STAGED(64, 8, true);
+    else LBFSS_LAUNCH_STAGED(32, 8, ROWS);
+#undef LBFSS_LAUNCH_STAGED
 }
 
 template <typename T, bool ROWS>
-void launch_fused_staged(const RepDesc *desc, const FusedTile *tiles, int n_tiles, const T *in, T *out,
-                         const uint64_t *step, int koff, int *err, int tx, int ty, hipStream_t stream, float *snap,
-                         int64_t total) {
-    if (snap)
-        launch_staged_snap<T, ROWS, true>(desc, tiles, n_tiles, in, out, step, koff, err, tx, ty, stream, snap, total);
-    else
-        launch_staged_snap<T, ROWS, false>(desc, tiles, n_tiles, in, out, step, koff, err, tx, ty, stream, snap,
-                                           total);
+void launch_fused_staged(const StagedArgs &a, int tx, int ty, bool drain, const T *in, T *out) {
+    if (a.snap && drain) launch_staged_tile<T, ROWS, true, true>(a, tx, ty, in, out);
+    else if (a.snap) launch_staged_tile<T, ROWS, true, false>(a, tx, ty, in, out);
+    else if (drain) launch_staged_tile<T, ROWS, false, true>(a, tx, ty, in, out);
+    else launch_staged_tile<T, ROWS, false, false>(a, tx, ty, in, out);
 }
 
 }  // namespace lbfss

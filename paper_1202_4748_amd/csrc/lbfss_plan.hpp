@@ -75,4 +75,35 @@ inline int make_fused_tiles(const std::vector<int> &Ls, int tx, int ty, int tz, 
     return 0;
 }
 
+// Most sites in rows that are no whole 64 bytes (FP16: 32)?
+inline bool ragged_rows(const std::vector<int> &Ls) {
+    int64_t sites = 0, ragged = 0;
+    for (int L : Ls) {
+        sites += (int64_t)L * L * L;
+        if (L % 16) ragged += (int64_t)L * L * L;
+    }
+    return 2 * ragged > sites;
+}
+
+// Do the staged tiles (tx, ty), n of them, run drained (k_fused_staged)?  Us a
+// step, copies left in flight against drained.
+inline bool drained_plan(const std::vector<int> &Ls, bool fp16, int tx, int ty, int64_t n, bool snap) {
+    const int maxL = *std::max_element(Ls.begin(), Ls.end());
+    const bool ragged = ragged_rows(Ls);
+    // ragged FP16 rows: 504^3 4800, 4299, 264^3 745, 699, 216^3 417, 432 on 64 x 8
+    // tiles; 168^3 230, 217 on 32 x 8.  Others: 512^3 3547, 3810, 240^3 465, 490
+    if (fp16) return ragged && (tx * ty < 512 || maxL >= 232);
+    // ragged FP32 rows on tiles of 256 threads: 132^3 149, 136, 220^3 814, 760 on
+    // 32 x 8; 196^3 521, 466, 132^3 165, 173 on 64 x 4; fewer tiles than two on
+    // most CUs: 116^3 95, 98.  Whole rows: 256^3 715, 763
+    if (tx * ty < 512) return ragged && n > 480 && (tx < 64 || maxL >= 196);
+    // 64 x 8: ragged rows 308^3 1749, 1670, 404^3 3821, 3644, 300^3 1482, 1504; and
+    // where all tiles are resident at once, nearly two on each CU: 256^3 630, 606,
+    // 228^3 648, 584, 240^3 547, 532, 192^3 276, 273 in one round, 192^3 in six
+    // slabs (288 tiles) 392, 394, 256^3 in 16-plane slabs 645, 671; not with the
+    // snapshot's stores (256^3 798, 853) nor in FP16 (256^3 438, 473) or with the
+    // equilibrium model (256^3 562, 617)
+    return (ragged && maxL >= 308) || (!snap && n > 384 && n <= 512);
+}
+
 }  // namespace lbfss
