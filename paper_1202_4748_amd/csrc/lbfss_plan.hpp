@@ -21,9 +21,11 @@ constexpr int kXcds = 8;
 // with empty tiles (nz = 0).  Replicas, the largest first, go whole to the XCD
 // with the least work so far where that leaves the fullest one within 5% of
 // the even share (96-replica sweep on 32 x 8 x 12: 136 us a step with its
-// tiles in one run, 130 us dealt whole); where it does not, the lists are runs
-// of equal work over all tiles, cut where they end (2 x 256^3: whole replicas
-// would keep two XCDs of eight, 3597 us a step against 1247 in one run).
+// tiles in one run, 130 us dealt whole), or where the tiles are blocks and the
+// fullest one has a CU for each (7 x 16^3 in 16 x 8 x 1: 7.8 us cut, 7.4 whole:
+// neighbours share an L2); where it does not, the lists are runs of equal work
+// over all tiles, cut where they end (2 x 256^3: whole replicas would keep two
+// XCDs of eight, 3597 us a step against 1247 in one run).
 inline int make_fused_tiles(const std::vector<int> &Ls, int tx, int ty, int tz, std::vector<FusedTile> &out) {
     if (tx < 1 || ty < 1 || tz < 1 || tz > 1024) return -1;
     out.clear();
@@ -59,7 +61,10 @@ inline int make_fused_tiles(const std::vector<int> &Ls, int tx, int ty, int tz, 
             work[k] += work_of(run[first]);
         }
     }
-    if (20 * kXcds * *std::max_element(work.begin(), work.end()) > 21 * total) {
+    size_t fullest = 0;
+    for (const auto &l : lists) fullest = std::max(fullest, l.size());
+    const bool one_each = tz <= 4 && fullest <= 32;
+    if (!one_each && 20 * kXcds * *std::max_element(work.begin(), work.end()) > 21 * total) {
         for (auto &l : lists) l.clear();
         int64_t before = 0;
         for (const FusedTile &t : run) {  // by the middle of the tile's share of the run

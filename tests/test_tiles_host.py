@@ -70,3 +70,15 @@ def test_equal_replicas_are_hardly_padded(table, Ls):
     t = table((32, 8, 12), Ls)
     n = sum(1 for k in t if k[6])
     assert len(t) <= 1.1 * n + 8
+
+
+@pytest.mark.parametrize("tile,Ls,whole", [((16, 8, 1), [16] * 7, True), ((16, 8, 1), [16] * 8, True),
+                                           ((32, 4, 4), [8] * 33, True), ((16, 8, 4), [32] * 2, False),
+                                           ((32, 8, 16), [64] * 2, False)])
+def test_blocks_with_a_cu_each_stay_together(table, tile, Ls, whole):
+    """Block plans whose fullest list has a CU for every block keep replicas on
+    one XCD; more blocks, and marching tiles, are cut."""
+    t = table(tile, Ls)
+    per = len(t) // 8
+    where = [{x for x in range(8) for k in t[x * per:(x + 1) * per] if k[6] and k[0] == r} for r in range(len(Ls))]
+    assert all(len(w) == 1 for w in where) is whole
