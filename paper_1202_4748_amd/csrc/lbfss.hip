@@ -151,14 +151,7 @@ struct lb_sim {
     bool pending = false;
 };
 
-// The rows staging copies 16-byte chunks that must not straddle the periodic
-// seam: every lattice edge a multiple of 4 (FP32) or 8 (FP16 storage).
-static bool rows_ok(const lb_sim *s) {
-    const int ch = s->storage == LB_FP16 ? 8 : 4;
-    for (const auto &d : s->hdesc)
-        if (d.L % ch) return false;
-    return true;
-}
+static bool rows_ok(const lb_sim *s) { return rows_edges(s->L, s->storage == LB_FP16); }
 
 namespace {
 
@@ -742,78 +735,6 @@ int build_tiles(lb_sim *s, int tx, int ty, int tz) {
     return LB_OK;
 }
 
-// Blocks (or tiles) of a shape over all replicas, and the sites they span.
-void count_tiles(const lb_sim *s, int tx, int ty, int tz, int64_t *n, int64_t *span) {
-    *n = *span = 0;
-    for (int L : s->L) {
-        const int64_t c = ceil_div(L, tx) * ceil_div(L, ty) * ceil_div(L, tz);
-        *n += c;
-        *span += c * tx * ty * tz;
-    }
-}
-
-// The plan of a new handle, by size: blocks while they are resident in one
-// round of the 256 CUs, then two passes, then marching tiles (us a step,
-// force model FP32 unless stated).
-lb_plan default_plan(const lb_sim *s) {
-    const bool rows = rows_ok(s), fp16 = s->storage == LB_FP16;
-    const int64_t T = s->total_sites;
-    const int maxL = s->max_L, march = rows ? LB_KERNEL_ROWS : LB_KERNEL_FUSED;
-    int64_t n, span;
-    if (s->eq_pressure) {
-        if (!rows) return lb_plan{LB_KERNEL_SPLIT, 0, 0, 0, 0, 0};
-        // 32^3: 7.4, marching 45; 64^3: 13.3, 46; 112^3: 59 against 70; 128^3: 113 against 80
-        count_tiles(s, 32, 8, 1, &n, &span);
-        if (n <= 256) return lb_plan{march, 32, 8, 1, 0, 0};
-        if (T < 118 * 118 * 118) return lb_plan{march, 32, 8, 2, 0, 0};
-    } else {
-        // 32^3: 7.7 as 256 blocks of 16 x 8 x 1, 8.7 as 128 of twice the
-        // depth, 10.3 in three passes, marching 54
-        count_tiles(s, 16, 8, 1, &n, &span);
-        if (n <= 256) return lb_plan{march, 16, 8, 1, 0, 0};
-        // deeper blocks where the lattice's edge leaves few of their threads
-        // idle: 48^3 12.1 against 15.2 in two passes (40^3, padded by a
-        // fifth: 13.4 against 11.4), 64^3 15.4 against 16.2 (FP16 13.5, 15.9)
-        for (int tx : {16, 32}) {
-            count_tiles(s, tx, 8, 4, &n, &span);
-            if (n <= 256 && 5 * span < 6 * T) return lb_plan{march, tx, 8, 4, 0, 0};
-        }
-        // two passes read the populations twice, but every CU is at work:
-        // 96^3 38 against 51 on the best marching tiles, 144^3 147 against
-        // 156, 160^3 192 against 198, 176^3 279 against 237; FP16 112^3 54
-        // against 58, 128^3 69 against 60.  Without rows staging (an edge
-        // that is no multiple of 4, FP16 of 8) they stay ahead: 250^3 844
-        // against 1183.  A batch of small lattices marches from 2^21 sites
-        // (96-replica sweep: 130 against 139).
-        const int64_t two = fp16 ? 116 * 116 * 116 : (maxL < 128 ? 128 * 128 * 128 : 161 * 161 * 161);
-        if (!rows || T < two) return lb_plan{LB_KERNEL_SPLIT, 0, 0, 0, 0, 0};
-    }
-    lb_plan p{LB_KERNEL_ROWS, 32, 8, 12, 0, 0};  // sweep: 12 planes 130, 16 planes 147, 8 planes 135
-    if (maxL < 116) return p;
-    // 64 x 8 tiles stage the fewest halo rows a site (512 threads, two
-    // workgroups per CU); below 256 FP32 they give way to 32 x 8 where the
-    // last tile of a row would be mostly empty (224^3: 498 against 515)
-    const int64_t wide_span = ceil_div(maxL, 64) * 64;
-    if (!fp16 && maxL < 256 && 8 * wide_span > 9 * maxL) {
-        p.tile_z = 16;
-        return p;
-    }
-    p.tile_x = 64;
-    // shallow slabs until their tiles fill the chip: 128^3 eq 80.7 in eight
-    // planes, 81.8 in sixteen, 136 in 32; 192^3 309 in sixteen, 303 in 32,
-    // 340 in 64 on 64 x 4 tiles; 240^3 618 in sixteen, 586 in 32
-    if (maxL <= 128) p.tile_z = 8;
-    else if (maxL < 224 || (fp16 && maxL < 256)) p.tile_z = 16;
-    else if (s->eq_pressure) p.tile_z = (maxL + 7) / 8;  // 256^3: eight slabs 551; three 5% slower
-    else if (fp16) p.tile_z = (maxL + 5) / 6;
-    else if (maxL < 256) p.tile_z = 32;
-    // four slabs while one layer of tiles cannot fill a round of two
-    // workgroups per CU (256^3: 512 tiles, one round), else six (512^3: 7%
-    // faster than four)
-    else p.tile_z = ceil_div(maxL, 64) * ceil_div(maxL, 8) >= 512 ? (maxL + 5) / 6 : (maxL + 3) / 4;
-    return p;
-}
-
 int create_impl(int n, const int *L, const lb_params *p, const uint64_t *seeds, lb_sim **out) {
     if (!out || n < 1 || !L || !p || !seeds) return LB_EINVAL;
     *out = nullptr;
@@ -900,7 +821,7 @@ int create_impl(int n, const int *L, const lb_params *p, const uint64_t *seeds, 
     if (hipGetLastError() != hipSuccess) return fail(LB_EDEVICE);
     if ((rc = build_sampling(s))) return fail(rc);
     if ((rc = build_sk3(s))) return fail(rc);
-    lb_plan def = default_plan(s);
+    lb_plan def = default_plan(s->L, s->storage == LB_FP16, s->eq_pressure);
     if (lb_set_plan(s, &def) != LB_OK) {
         lb_plan split{LB_KERNEL_SPLIT, 0, 0, 0, 0, 0};
         if ((rc = lb_set_plan(s, &split))) return fail(rc);
@@ -1401,6 +1322,12 @@ int lb_tune(lb_sim *s, int steps, lb_plan *best) {
         if (rows_tile_ok(t[0], t[1]) && rows_ok(s))
             cands.push_back(lb_plan{LB_KERNEL_ROWS, t[0], t[1], t[2], 0, 0});
     }
+    // the plan in place, whose depth may be none of those
+    const lb_plan own{s->plan.kernel, s->plan.tile_x, s->plan.tile_y, s->plan.tile_z, 0, 0};
+    if (std::none_of(cands.begin(), cands.end(), [&](const lb_plan &c) {
+            return c.kernel == own.kernel && c.tile_x == own.tile_x && c.tile_y == own.tile_y && c.tile_z == own.tile_z;
+        }))
+        cands.push_back(own);
     const int64_t P = graph_period(s);
     const int gsteps = (int)(ceil_div(std::max<int64_t>(steps, 8), P) * P);
     hipEvent_t e0, e1;
