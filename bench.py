@@ -54,7 +54,8 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-STEP_KERNEL_SOURCES = ("lbfss_device.hpp", "lbfss_step.hpp", "lbfss_fused.hpp")
+# (lbfss_plan.hpp: the order of the tiles and which instance runs them)
+STEP_KERNEL_SOURCES = ("lbfss_device.hpp", "lbfss_step.hpp", "lbfss_fused.hpp", "lbfss_plan.hpp")
 
 
 def code_of(text):
@@ -74,6 +75,12 @@ def kernel_source_hash(csrc=None, names=STEP_KERNEL_SOURCES):
         with open(os.path.join(csrc, name)) as fh:
             h.update(code_of(fh.read()).encode())
     return h.hexdigest()[:16]
+
+
+def sources_of(kernel, base=STEP_KERNEL_SOURCES):
+    """The sources that a kernel of a model (its marching kernels': base) is
+    built from."""
+    return base + ("lbfss_block.hpp",) if kernel == "k_block" else base
 
 
 def force_step_kernel(plan):
@@ -98,7 +105,9 @@ def read_traffic(kname, workload, storage, plan):
     m = re.search(r"source_hash:\s*([0-9a-f]+)", text)
     b = re.search(r"traffic_bytes_per_launch:\s*([0-9.eE+]+)", text)
     t = re.search(r"plan (\w+):(\d+):(\d+):(\d+):\d+", text)
-    if not m or not b or not t or m.group(1) != kernel_source_hash():
+    names = sources_of(kname)
+    key = kernel_source_hash() if names is STEP_KERNEL_SOURCES else kernel_source_hash(names=names)
+    if not m or not b or not t or m.group(1) != key:
         return None
     here = (KERNEL_NAMES[plan["kernel"]], plan["tile_x"], plan["tile_y"], plan["tile_z"])
     if (t.group(1), int(t.group(2)), int(t.group(3)), int(t.group(4))) != here:
@@ -245,7 +254,7 @@ def main():
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": traffic, "bytes_per_site": BYTES_PER_SITE[args.storage],
                      "valu_busy": read_valu_busy(kname, args.workload if args.workload.endswith("_" + args.storage)
-                                                 else f"{args.workload}_{args.storage}", STEP_KERNEL_SOURCES, kplan),
+                                                 else f"{args.workload}_{args.storage}", sources_of(kname), kplan),
                      "us_per_launch": round(ms_per_launch * 1e3, 2),
                      "device_copy_gbs": round(copy_gbs, 1), "frac_of_copy": round(achieved / copy_gbs, 4)},
         "mass": mom["mass"],
@@ -272,7 +281,7 @@ PAPER_MODEL = {
     "eq": ("D3Q19", 3, 19),
     "d2q9": ("D2Q9", 2, 9),
 }
-PAPER_MODEL_SOURCES = {"eq": ("lbfss_device.hpp", "lbfss_step.hpp", "lbfss_fused.hpp", "lbfss_meq.hpp"),
+PAPER_MODEL_SOURCES = {"eq": ("lbfss_device.hpp", "lbfss_step.hpp", "lbfss_fused.hpp", "lbfss_plan.hpp", "lbfss_meq.hpp"),
                        "d2q9": ("lbfss_device.hpp", "lbfss_fused.hpp", "lbfss_d2q9.hpp")}
 
 
@@ -300,7 +309,7 @@ def read_step_traffic(model, workload, kernels, plan=None):
     text = open(path).read()
     m = re.search(r"source_hash:\s*([0-9a-f]+)", text)
     b = re.search(r"traffic_bytes_per_step:\s*([0-9.eE+]+)", text)
-    if not m or not b or m.group(1) != kernel_source_hash(names=PAPER_MODEL_SOURCES[model]):
+    if not m or not b or m.group(1) != kernel_source_hash(names=sources_of(kernels[-1], PAPER_MODEL_SOURCES[model])):
         return None
     if plan is not None:
         t = re.search(r"plan (\w+:\d+:\d+:\d+)", text)
@@ -401,7 +410,8 @@ def bench_paper_model(args, wl, torch, lbf, workloads, stream):
         "roofline": {"bound": "hbm", "kernel": " + ".join(kernels), "achieved": round(achieved, 1),
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": read_step_traffic(model, args.workload, kernels, plan), "bytes_per_site": bps,
-                     "valu_busy": read_valu_busy(kernels[-1], args.workload, PAPER_MODEL_SOURCES[model], plan)
+                     "valu_busy": read_valu_busy(kernels[-1], args.workload,
+                                                 sources_of(kernels[-1], PAPER_MODEL_SOURCES[model]), plan)
                      if len(kernels) == 1 else None,
                      "us_per_step": round(ms_per_step * 1e3, 2), "device_copy_gbs": round(copy_gbs, 1),
                      "frac_of_copy": round(achieved / copy_gbs, 4)},
