@@ -199,12 +199,14 @@ typedef struct lb_sim lb_sim; /* opaque, owned by the library */
  * (site, 0, 1 << 16, 0), u = 0, f_i = w_i rho.  *out receives the handle
  * (owned by the library until lb_destroy); p is read during the call only.
  * Initial plan, by size: blocks (lb_plan, tile_z) while they fit one round of
- * the chip, LB_KERNEL_SPLIT up to 160^3 sites (115^3 in FP16, never with
- * LB_EQ_PRESSURE) and wherever the edges do not allow LB_KERNEL_ROWS, else
- * LB_KERNEL_ROWS: on 32 x 8 or 64 x 8 tiles, from L = 256 on 64 x 8 tiles in
- * four z slabs (six from L = 512 and in FP16, eight with LB_EQ_PRESSURE);
- * direct launches (lb_set_plan and lb_tune change it; results do not depend
- * on it).
+ * the chip (with LB_EQ_PRESSURE up to 117^3 sites), LB_KERNEL_SPLIT up to 160^3
+ * sites (127^3 in total where no edge reaches 128, 115^3 in FP16; not with
+ * LB_EQ_PRESSURE), wherever the edges do not allow LB_KERNEL_ROWS and on many
+ * edges that are no multiple of 16, else LB_KERNEL_ROWS: batches of edges below
+ * 116 on 32 x 8 tiles, else 64 x 8 tiles, up to L = 256 as deep as lets the chip
+ * hold all of them at once, beyond in four z slabs (six from L = 512 and in
+ * FP16, eight with LB_EQ_PRESSURE); direct launches (lb_set_plan and lb_tune
+ * change it; results do not depend on it).
  * Errors: LB_EINVAL for L < 4, L > 1024, tau <= 1/2, kT < 0, kappa < 0,
  * b < 0, rho_c <= 0, init_sigma < 0, bad storage, flags, sample_every < 0,
  * n_levels < 0 or series_capacity < 0; LB_ENOMEM; LB_EDEVICE. */

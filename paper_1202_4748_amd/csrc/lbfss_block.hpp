@@ -41,8 +41,8 @@ __device__ __forceinline__ int wrap_far(int v, int L, float rL) {
 // population's) plus a 32-bit byte offset (L <= 1024: 4 GiB a population).
 // MUL24: the row and plane offsets by the full-rate multiply (factors below
 // 2^24, products modulo 2^32).  A site of the FP32 force model's blocks pulls
-// up to six times and waits on these chains (16^3: 7.53 -> 7.25 us a step,
-// 32^3 8.06 -> 7.72, 64^3 15.6 -> 15.4); the other forms schedule worse with
+// up to six times and waits on these chains (16^3: 7.5 -> 7.2 us a step, 32^3
+// 8.1 -> 7.7, 64^3 15.9 -> 15.7); the other forms schedule worse with
 // it (FP16 64^3 13.5 -> 14.0, equilibrium model 13.2 -> 13.7).
 template <bool MUL24, typename T>
 __device__ __forceinline__ void pull_site(const T *base, uint32_t N, int L, int x, int y, int z, float (&r)[Q]) {

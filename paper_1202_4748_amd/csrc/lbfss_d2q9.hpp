@@ -250,8 +250,8 @@ __device__ __forceinline__ bool k2_collide_site(const D2Desc &D, float (&d)[Q2],
 constexpr int K2TX = 64, K2TY = 4;
 // Where the two copies of a batch exceed the 256 MB cache behind the L2s, no
 // line that is written is read again before it is evicted, and writing around
-// the caches leaves them to the reads: 64 x 256^2 68.3 -> 65.6 us, 128 x 256^2
-// 129.8 -> 125.5, 16 x 512^2 70.0 -> 66.1, 4 x 1024^2 69.5 -> 68.9.  Below that
+// the caches leaves them to the reads: 64 x 256^2 69.7 -> 65.9 us, 128 x 256^2
+// 131.9 -> 127.4, 16 x 512^2 71.3 -> 66.4, 4 x 1024^2 72.7 -> 68.6.  Below that
 // size it costs (56 x 256^2 47.4 -> 59.4), as it does for rows that are not
 // whole 128-byte lines (400 x 100^2 79.1 -> 84.2) and for 2048^2 (69.7 -> 70.4).
 inline bool k2_store_nt(int L, int nrep) {
